@@ -170,7 +170,24 @@ void write_scene(unsigned char* dst, const SceneLayout& L, const mppi_config& c,
     flags[0] = 1;
     for (int i = 1; i < sc->n_waypoints; ++i)
         if (vr[i] != vr[0]) flags[0] = 0;
-    flags[1] = flags[2] = flags[3] = 0;
+    // the waypoint nearest to the origin and the inverse of the mean spacing of
+    // those that follow it: where the scan by rows starts looking
+    int j0 = 0;
+    float near2 = INFINITY;
+    for (int i = 0; i < sc->n_waypoints; ++i) {
+        const float d2 = xy[i].x * xy[i].x + xy[i].y * xy[i].y;
+        if (d2 < near2) {
+            near2 = d2;
+            j0 = i;
+        }
+    }
+    const int ja = std::max(std::min(j0, sc->n_waypoints - 1 - kChunk), 0);
+    const int jb = std::min(ja + kChunk, sc->n_waypoints - 1);
+    const float len = hypotf(xy[jb].x - xy[ja].x, xy[jb].y - xy[ja].y);
+    const float inv_sp = len > 1e-6f ? (float)(jb - ja) / len : 0.0f;
+    flags[1] = j0;
+    memcpy(&flags[2], &inv_sp, sizeof inv_sp);
+    flags[3] = 0;
     for (int i = 0; i < sc->n_circles; ++i) {
         const double* o = sc->circles + 5 * i;
         pv[i] = make_float4((float)(o[0] - origin[0]), (float)(o[1] - origin[1]), (float)o[3],
@@ -229,7 +246,7 @@ static void load_tuning()
         t.occ = 0;
         const int n = sscanf(line, "%d %d %d %d %d %d", &t.k, &t.t, &t.c, &t.lanes, &t.stage,
                              &t.occ);
-        if (n >= 4 && (t.stage == 0 || t.stage == 1) && t.occ >= 0 && t.occ < kOccModes &&
+        if (n >= 4 && (t.stage == 0 || t.stage == 1) && t.occ >= 0 && t.occ <= kOccHigh &&
             (t.lanes == 1 || t.lanes == 2 || t.lanes == 4 || t.lanes == 8 || t.lanes == 16))
             g_tune.push_back(t);
     }
@@ -281,11 +298,17 @@ int auto_occ(const mppi_config& c, int n_c)
     return e ? e->occ : 0;
 }
 
-int occ_choice(const mppi_t* h, int n_c, int lanes)
+int occ_choice(const mppi_t* h, int n_wp, int n_c, int lanes, bool alone)
 {
+    const mppi_config& c = h->cfg;
+    if (lanes == 16 && !h->no_cull && h->occ_req < 0) {
+        const size_t lds = split_layout(c.T, n_wp, c.per_step_weights).total;
+        const bool one_each = alone && c.K <= 16 * 256;  // at most a tile per compute unit
+        if (lds <= kSplitLds || (one_each && lds <= kSplitLdsAlone)) return kOccSplit;
+    }
     // the other compilations exist for 8 and 16 lanes per sample
     if (lanes < 8) return kOccDefault;
-    return h->occ_req >= 0 ? h->occ_req : auto_occ(h->cfg, n_c);
+    return h->occ_req >= 0 ? h->occ_req : auto_occ(c, n_c);
 }
 
 // ---- profiling --------------------------------------------------------------------
@@ -456,7 +479,7 @@ mppi_status handle_create(const mppi_config* cfg, void* hip_stream, bool with_sc
         h->own_stream = true;
     }
     if ((e = hipMalloc((void**)&h->U, sizeof(double) * 2 * T)) != hipSuccess ||
-        (e = hipMalloc((void**)&h->st, state_bytes(h->max_tiles))) != hipSuccess)
+        (e = hipMalloc((void**)&h->st, sizeof(DevState))) != hipSuccess)
         return bail(MPPI_E_NOMEM, "hipMalloc", e);
     if (with_scratch) {
         struct { void** p; size_t n; } allocs[] = {
@@ -484,7 +507,7 @@ mppi_status handle_create(const mppi_config* cfg, void* hip_stream, bool with_sc
             return bail(MPPI_E_DEVICE, "initialise device state", e);
     }
     if ((e = hipMemsetAsync(h->U, 0, sizeof(double) * 2 * T, h->stream)) != hipSuccess ||
-        (e = hipMemsetAsync(h->st, 0, state_bytes(h->max_tiles), h->stream)) != hipSuccess ||
+        (e = hipMemsetAsync(h->st, 0, sizeof(DevState), h->stream)) != hipSuccess ||
         (e = hipStreamSynchronize(h->stream)) != hipSuccess)
         return bail(MPPI_E_DEVICE, "initialise device state", e);
     if (const char* env = getenv("MPPI_LANES_PER_SAMPLE")) {
@@ -511,7 +534,8 @@ void choose_eps_stage(InstDesc& d, bool alone, int allowed)
 }
 
 void fill_desc(InstDesc& d, const mppi_t* h, const double x0[4], const double origin[2],
-               const unsigned char* scene, const SceneLayout& L, int n_wp, int n_c, int shift)
+               const unsigned char* scene, const SceneLayout& L, int n_wp, int n_c, int shift,
+               bool alone)
 {
     const mppi_config& c = h->cfg;
     memset(&d, 0, sizeof d);
@@ -524,7 +548,7 @@ void fill_desc(InstDesc& d, const mppi_t* h, const double x0[4], const double or
     // two or more waves per SIMD (256 compute units x 4): the block-ordered
     // wave priority pays; with fewer it only costs its instructions
     d.wave_prio = (long)c.K * d.lanes >= 2L * 1024 * 64 ? 1 : 0;
-    d.occ = occ_choice(h, n_c, d.lanes);
+    d.occ = occ_choice(h, n_wp, n_c, d.lanes, alone);
     d.dt = (float)c.dt;
     d.inv_dt = (float)(1.0 / c.dt);
     d.inv_L = (float)(1.0 / c.wheelbase);
@@ -577,7 +601,7 @@ void fill_desc(InstDesc& d, const mppi_t* h, const double x0[4], const double or
     d.q = h->q;
     d.Stk = h->Stk;
     d.st = h->st;
-    choose_eps_stage(d, false, stage_allowed(h, n_c));
+    choose_eps_stage(d, alone, stage_allowed(h, n_c));
 }
 
 // ---- batched launches ---------------------------------------------------------------
@@ -689,8 +713,9 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
         const int g = hs[i]->lanes_req ? hs[i]->lanes_req : auto_lanes(c, nc);
         const int gi = g == 1 ? 0 : g == 2 ? 1 : g == 4 ? 2 : g == 8 ? 3 : 4;
         order[i] = i;
-        cls[i] = 50 * occ_choice(hs[i], nc, g) + 25 * (c.model ? 1 : 0) + 5 * gi +
-                 active_ego(c.n_ego, nc);
+        const int occ = occ_choice(hs[i], nw, nc, g, false);
+        cls[i] = 50 * occ + 25 * (c.model ? 1 : 0) +
+                 5 * (occ == kOccSplit ? (c.per_step_weights ? 3 : 4) : gi) + active_ego(c.n_ego, nc);
         work[i] = (double)c.T * (73.0 + 6.0 * nw + 7.0 * c.n_ego * nc);
     }
     std::stable_sort(order.begin(), order.end(), [&](int a, int c) {
@@ -700,8 +725,8 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
     int* prefix = reinterpret_cast<int*>(host + off_prefix);
     InstDesc* descs = reinterpret_cast<InstDesc*>(host + off_descs);
     long total = 0;
-    size_t smem = 0;
-    int any_shift = 0, any_out = 0, combine_g = 0, max_nodes = 0;
+    size_t smem = 0, smem_split = 0;
+    int any_shift = 0, any_out = 0, combine_g = 0, max_nodes = 0, most_tiles = 0;
     for (int j = 0; j < n; ++j) {
         const int i = order[j];
         mppi_t* hi = hs[i];
@@ -712,9 +737,10 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
             const double origin[2] = {x0[0], x0[1]};
             write_scene(host + soff[i], lay[i], hi->cfg, origin, &scenes[i]);
             fill_desc(descs[j], hi, x0, origin, ws->arena + soff[i], lay[i], scenes[i].n_waypoints,
-                      scenes[i].n_circles, sh);
+                      scenes[i].n_circles, sh, false);
         } else {
-            fill_desc(descs[j], hi, x0, hi->origin, hi->scene, hi->lay, hi->n_wp, hi->n_c, sh);
+            fill_desc(descs[j], hi, x0, hi->origin, hi->scene, hi->lay, hi->n_wp, hi->n_c, sh,
+                      false);
         }
         if (ex) {
             descs[j].S = ex->S;
@@ -727,12 +753,12 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
         }
         prefix[j] = (int)total;
         total += descs[j].n_tiles;
-        smem = std::max(smem, lds_layout(descs[j].n_wp, descs[j].n_c, descs[j].T,
-                                         kBlock / descs[j].lanes, descs[j].eps_stage,
-                                         descs[j].per_step, !descs[j].cull).total);
+        size_t& lds = descs[j].occ == kOccSplit ? smem_split : smem;
+        lds = std::max(lds, iteration_lds(descs[j]));
         any_shift |= sh;
         combine_g = std::max(combine_g, combine_groups(descs[j].T));
         max_nodes = std::max(max_nodes, combine_nodes(descs[j].n_tiles, nullptr));
+        if (!descs[j].per_step) most_tiles = std::max(most_tiles, descs[j].n_tiles);
     }
     if (total > (1L << 30)) return fail(MPPI_E_INVALID, "batch too large");
     prefix[n] = (int)total;
@@ -751,8 +777,10 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
         }
         hdr->cls_begin[kLaneClasses] = n;
     }
-    const size_t smem_b = align_up(smem, 4096);
+    const size_t smem_b = align_up(smem, 4096), smem_s = align_up(smem_split, 4096);
     const int node_limit = max_nodes <= kDirectSmall ? kDirectSmall : kDirect;
+    // the merge's grid, rounded up like the others (0: nothing to merge)
+    const int merge_tiles = most_tiles > kDirect ? (int)pow2_at_least((size_t)most_tiles, 1) : 0;
     const int n_blocks = (int)pow2_at_least((size_t)n, 1);
     const int shift_blocks = any_shift ? n_blocks : 0;
     const int gather_blocks = (gather_dev && any_out) ? n_blocks : 0;
@@ -762,9 +790,10 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
         if (e == hipSuccess && shift_blocks) e = launch_shift_batch(hdr_dev, shift_blocks, stream);
         for (int c = 0; c < kLaneClasses && e == hipSuccess; ++c)
             if (grids[c] > 0)
-                e = launch_batch(kClassLanes[(c % 25) / 5], c % 5, (c % 50) / 25, c / 50, nullptr,
-                                 hdr_dev, c,
-                                 grids[c], smem_b, stream);
+                e = launch_batch(kClassLanes[(c % 25) / 5], c % 5, (c % 50) / 25, c / 50, (c % 25) / 5 == 3,
+                                 nullptr, hdr_dev, c, grids[c], c / 50 == kOccSplit ? smem_s : smem_b,
+                                 stream);
+        if (e == hipSuccess) e = launch_merge(nullptr, hdr_dev, merge_tiles, n_blocks, stream);
         if (e == hipSuccess && combine_g)
             e = launch_combine(nullptr, hdr_dev, combine_g, n_blocks, max_nodes, stream);
         if (e == hipSuccess && gather_blocks)
@@ -778,10 +807,10 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
     if (use_graph && graphs_enabled()) {
         GraphEntry* ge = nullptr;
         for (GraphEntry& g : ws->graphs)
-            if (g.bytes == bucket && g.smem == smem_b && g.buf == b &&
+            if (g.bytes == bucket && g.smem == smem_b && g.smem_split == smem_s && g.buf == b &&
                 g.shift_blocks == shift_blocks && g.gather_blocks == gather_blocks &&
                 g.combine_g == combine_g && g.combine_y == (combine_g ? n_blocks : 0) &&
-                g.combine_nodes == node_limit && memcmp(g.grids, grids, sizeof grids) == 0)
+                g.combine_nodes == node_limit && g.merge_tiles == merge_tiles && memcmp(g.grids, grids, sizeof grids) == 0)
                 ge = &g;
         if (!ge) {
             if (ws->graphs.size() >= 64) {
@@ -792,6 +821,7 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
             GraphEntry g;
             g.bytes = bucket;
             g.smem = smem_b;
+            g.smem_split = smem_s;
             memcpy(g.grids, grids, sizeof grids);
             g.buf = b;
             g.shift_blocks = shift_blocks;
@@ -799,6 +829,7 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
             g.combine_g = combine_g;
             g.combine_y = combine_g ? n_blocks : 0;
             g.combine_nodes = node_limit;
+            g.merge_tiles = merge_tiles;
             g.graph = nullptr;
             g.exec = nullptr;
             HIP_TRY(hipStreamBeginCapture(stream, hipStreamCaptureModeThreadLocal));
@@ -901,18 +932,15 @@ mppi_status mppi_step_resident(mppi_t* h, const double x0[4])
     for (int i = 0; i < 4; ++i)
         if (!isfinite(x0[i])) return fail(MPPI_E_INVALID, "x0[%d] is not finite", i);
     InstDesc d;
-    fill_desc(d, h, x0, h->origin, h->scene, h->lay, h->n_wp, h->n_c, 0);
-    choose_eps_stage(d, true, stage_allowed(h, h->n_c));
-    const size_t smem =
-        lds_layout(d.n_wp, d.n_c, d.T, kBlock / d.lanes, d.eps_stage, d.per_step, !d.cull).total;
+    fill_desc(d, h, x0, h->origin, h->scene, h->lay, h->n_wp, h->n_c, 0, true);
     hipEvent_t a = nullptr;
     if ((s = record_launch(h, 0, &a)) != MPPI_OK) return s;
     hipEvent_t a2 = nullptr;
     if ((s = record_launch(h, 2, &a2)) != MPPI_OK) return s;
-    HIP_TRY(launch_batch(d.lanes, active_ego(d.n_ego, d.n_c), d.model, d.occ, &d, nullptr, 0,
-                         d.n_tiles,
-                         smem, h->stream));
+    HIP_TRY(launch_batch(d.lanes, active_ego(d.n_ego, d.n_c), d.model, d.occ, d.per_step, &d, nullptr, 0,
+                         d.n_tiles, iteration_lds(d), h->stream));
     if ((s = record_end(h, 2, a2)) != MPPI_OK) return s;
+    if (!d.per_step) HIP_TRY(launch_merge(&d, nullptr, d.n_tiles, 1, h->stream));
     HIP_TRY(launch_combine(&d, nullptr, combine_groups(d.T), 1, combine_nodes(d.n_tiles, nullptr),
                            h->stream));
     if ((s = record_end(h, 0, a)) != MPPI_OK) return s;
@@ -1169,7 +1197,7 @@ mppi_status mppi_set_occupancy(mppi_t* h, int32_t mode)
 {
     mppi_status s = usable(h);
     if (s != MPPI_OK) return s;
-    if (mode < -1 || mode >= kOccModes)
+    if (mode < -1 || mode > kOccHigh)
         return fail(MPPI_E_INVALID, "occupancy mode must be -1, 0 or 1");
     h->occ_req = mode;
     return MPPI_OK;

@@ -18,9 +18,10 @@ mppi_status fail(mppi_status s, const char* fmt, ...) __attribute__((format(prin
 
 // A captured batch launch: arena copy + kernels, for one size class.
 struct GraphEntry {
-    size_t bytes, smem;
+    size_t bytes, smem, smem_split;
     int grids[kLaneClasses];
     int buf, shift_blocks, gather_blocks, combine_g, combine_y;
+    int merge_tiles;    // the tile count the merge is launched for (0: none)
     int combine_nodes;  // the combine width's node limit (kDirectSmall or kDirect)
     hipGraph_t graph;
     hipGraphExec_t exec;
@@ -134,13 +135,6 @@ namespace mppi_impl {
     } while (0)
 
 SceneLayout scene_layout(int n_wp, int n_c);
-// Bytes of a handle's device state: DevState and the partial-tree tickets
-// for up to max_tiles tiles.
-inline size_t state_bytes(int max_tiles)
-{
-    return sizeof(DevState) +
-           sizeof(unsigned int) * kTicketStride * ((size_t)combine_tickets(max_tiles) + 1);
-}
 void write_scene(unsigned char* dst, const SceneLayout& L, const mppi_config& c,
                  const double origin[2], const mppi_scene* sc);
 mppi_status validate_scene(const mppi_config& c, const double x0[4], const mppi_scene* sc);
@@ -151,7 +145,8 @@ size_t pow2_at_least(size_t v, size_t lo);
 mppi_status record_launch(mppi_t* h, int kind, hipEvent_t* a);
 mppi_status record_end(mppi_t* h, int kind, hipEvent_t a);
 void fill_desc(InstDesc& d, const mppi_t* h, const double x0[4], const double origin[2],
-               const unsigned char* scene, const SceneLayout& L, int n_wp, int n_c, int shift);
+               const unsigned char* scene, const SceneLayout& L, int n_wp, int n_c, int shift,
+               bool alone);
 // Whether the tiles of d keep their perturbations in LDS: within kLdsShared,
 // or within kLdsAlone for an instance launched alone (alone = true) with at
 // most 512 tiles.
@@ -160,11 +155,12 @@ void choose_eps_stage(InstDesc& d, bool alone, int allowed);
 // the tuning table's choice for its shape).
 int stage_allowed(const mppi_t* h, int n_c);
 int auto_stage(const mppi_config& c, int n_c);
-// The compilation of the iteration kernel an instance is launched with: the
-// tuning table's choice (kOccDefault when it has no such column) unless the
-// handle requests one; kOccDefault below 8 lanes per sample.
+// The iteration kernel an instance is launched with, alone or in a batch: the
+// handle's request (a compilation of k_batch), else the split kernel where it
+// applies, else the tuning table's choice (kOccDefault when it has no such
+// column; kOccDefault below 8 lanes per sample).
 int auto_occ(const mppi_config& c, int n_c);
-int occ_choice(const mppi_t* h, int n_c, int lanes);
+int occ_choice(const mppi_t* h, int n_wp, int n_c, int lanes, bool alone);
 mppi_status ws_create(BatchWs** out);
 void ws_destroy(BatchWs* b);
 // Create a handle; with_scratch = false leaves S/eps/partials/scales/scene

@@ -15,9 +15,6 @@ constexpr int kMaxCircles = 1024;
 constexpr int kMaxK = 1 << 24;
 
 // Per-instance state that stays resident on the device between iterations.
-// The allocation continues with the group tickets of the in-kernel partial
-// tree (combine_tickets(max tiles) tickets of kTicketStride unsigned ints
-// each, zero between iterations).
 struct DevState {
     unsigned long long n_iter;  // Philox counter words 2-3: iteration number
     unsigned int reserved;
@@ -57,29 +54,16 @@ inline __host__ __device__ size_t partial_doubles(int T, int per_step, size_t ti
 }
 
 // Tile partials are merged by the combine kernel, which takes up to kDirect
-// rows in one pass.  Larger instances first merge their tiles inside the
-// iteration kernel by a tree of fixed shape: a node of level l + 1 merges up
-// to kFanIn consecutive nodes of level l, until at most kDirect nodes
-// remain.  Each group has a ticket; the member that completes it merges the
-// group into the row of its first tile.  The shape depends on the tile count
-// only.
+// rows in one pass.  Larger instances first merge their tiles by a tree of
+// fixed shape (k_merge, a launch per level): a node of level l + 1 merges up
+// to kFanIn consecutive nodes of level l, until at most kDirect nodes remain.
+// The shape depends on the tile count only.
 constexpr int kDirect = 2048;
 // The combine kernel comes in two widths: up to kDirectSmall nodes (two heads
 // per thread) and up to kDirect (eight per thread); a launch takes the
 // narrowest that holds its largest instance.
 constexpr int kDirectSmall = 512;
 constexpr int kFanIn = 16;
-// Tickets sit on separate 128-byte lines so that groups finishing at the same
-// time do not contend for one line.
-constexpr int kTicketStride = 32;
-
-inline __host__ __device__ int combine_tickets(int n_tiles)
-{
-    int total = 0;
-    for (int n = n_tiles; n > kDirect; n = (n + kFanIn - 1) / kFanIn) total += (n + kFanIn - 1) / kFanIn;
-    return total;
-}
-
 // Nodes left for the combine kernel and the tiles each one spans.
 inline __host__ __device__ int combine_nodes(int n_tiles, size_t* span)
 {
@@ -140,7 +124,7 @@ struct InstDesc {
     int per_step;         // 1: weights from the cost-to-go per step
     int eps_stage;        // 1: tiles keep their perturbations in LDS (lds_layout)
     int wave_prio;        // 1: wave priority falls with the block index (see iteration_tile)
-    int occ;              // compilation it is launched with, kOccDefault or kOccHigh (host-side)
+    int occ;              // iteration kernel it is launched with, kOcc... (host-side)
     int model;            // 1: 5-state model of eq. (5), steering-rate control
     float steer0;         // its initial steering angle
     float ego_ext;        // max |ego_off|
@@ -160,24 +144,25 @@ struct InstDesc {
     float* q;             // [T][K] stage costs (per-step weights)
     double* Stk;          // [T][K] cost-to-go (per-step weights; row 0 always, the
                           // other rows only when a tile works in global memory)
-    DevState* st;         // followed by the partial-tree tickets
+    DevState* st;
 };
 
-// Compilations of the iteration kernel (the "occupancy" launch choice): the
-// default one, and one for kHiOccWaves waves per SIMD (8 and 16 lanes per
-// sample only).
+// Iteration kernels (the "occupancy" launch choice): the default compilation
+// of k_batch, the one for kHiOccWaves waves per SIMD (8 and 16 lanes per
+// sample only), and the split kernel (16 lanes per sample, culling on).
 constexpr int kOccDefault = 0;
 constexpr int kOccHigh = 1;
-constexpr int kOccModes = 2;
+constexpr int kOccSplit = 2;
+constexpr int kOccModes = 3;
 constexpr int kHiOccWaves = 5;
 
 // Header of a batch arena in device memory: followed by the tile prefix
 // (n_inst + 1 ints) at off_prefix and the descriptors at off_descs.
 // Instances are grouped by kernel variant: class c = 50 * occ + 25 * model +
-// 5 * lane_index + ne (occ the compilation, kOccDefault or kOccHigh; model 0
-// or 1 (5-state); lane_index 0..4 for 1, 2, 4, 8, 16 lanes per sample; ne =
-// ego circles that meet obstacle circles, 0..4) owns instances
-// [cls_begin[c], cls_begin[c+1]).
+// 5 * lane_index + ne (occ the iteration kernel; model 0 or 1 (5-state);
+// lane_index 0..4 for 1, 2, 4, 8, 16 lanes per sample, of the split kernel 4
+// with total-cost and 3 with per-step weights; ne = ego circles that meet
+// obstacle circles, 0..4) owns instances [cls_begin[c], cls_begin[c+1]).
 constexpr int kLaneClasses = 50 * kOccModes;
 struct BatchHdr {
     int n_inst;
@@ -252,13 +237,72 @@ inline __host__ __device__ LdsLayout lds_layout(int n_wp, int n_c, int T, int sp
     return L;
 }
 
+// The split iteration kernel (mppi_split.hip): a wave of a group of four
+// samples walks, one scans the waypoints and, with ego circles and obstacles,
+// one the circles; the walker's states pass through a ring of kRing blocks of
+// 16 steps.
+constexpr int kRing = 4;
+inline __host__ __device__ constexpr int split_threads(int ne) { return kBlock * (ne > 0 ? 3 : 2); }
+struct SplitLayout {
+    size_t state, circ, wxy, cost, safe, extra, eps, qs, ss, sk, counts, total;
+};
+inline __host__ __device__ SplitLayout split_layout(int T, int n_wp, int per_step)
+{
+    SplitLayout L;
+    size_t o = 0;
+    const size_t n = (size_t)kRing * kBlock;  // steps in the ring
+    L.state = o;  o += n * 16;
+    L.circ = o;   o += (size_t)(kBlock / 64) * 65 * 32;
+    L.wxy = o;    o += (size_t)((n_wp + kChunk - 1) / kChunk) * kChunk * 8;
+    L.cost = o;   o += n * 4;
+    L.safe = o;   o += n * 4;
+    L.extra = o;  o += n * 4;
+    // the cost-to-go is formed once the ring is free, and takes its place
+    // where it fits
+    const size_t ss = per_step ? (size_t)T * (kBlock / 16 + 1) * 8 : 0;
+    L.ss = ss <= o ? 0 : o;
+    o += ss <= o ? 0 : ss;
+    L.eps = o;    o += (size_t)2 * T * (kBlock / 16 + 1) * 4;
+    o = align_up(o, 8);
+    L.qs = o;     o += per_step ? (size_t)T * (kBlock / 16 + 1) * 4 : 0;
+    L.sk = o;     o += kBlock / 16 * 4;
+    L.counts = o; o += 4 * (kBlock / 64) * 4;
+    L.total = align_up(o, 16);
+    return L;
+}
+// Two workgroups of the split kernel share a compute unit's 160 KB of LDS.
+// With more it is one, and k_batch's four are the faster again once every
+// unit has a tile.
+constexpr size_t kSplitLds = 80 << 10;
+constexpr size_t kSplitLdsAlone = 160 << 10;
+
+// Dynamic LDS of the iteration kernel of an instance.
+inline size_t iteration_lds(const InstDesc& d)
+{
+    return d.occ == kOccSplit ? split_layout(d.T, d.n_wp, d.per_step).total
+                              : lds_layout(d.n_wp, d.n_c, d.T, kBlock / d.lanes, d.eps_stage, d.per_step,
+                                           !d.cull).total;
+}
+
 // Launchers (mppi_kernels.hip).  All enqueue on `stream` and return the
 // launch error, if any.
 // Iteration kernel, one workgroup per tile: one instance (d0, hdr_dev ==
 // nullptr) or lanes class `cls` of the batch described by the arena at
 // hdr_dev (lanes is the launch shape of every instance it processes).
-hipError_t launch_batch(int lanes, int ne, int model, int occ, const InstDesc* d0,
+hipError_t launch_batch(int lanes, int ne, int model, int occ, int per_step, const InstDesc* d0,
                         const BatchHdr* hdr_dev, int cls, int grid, size_t smem,
+                        hipStream_t stream);
+
+
+// The split kernel, as launch_batch launches it (mppi_split.hip).
+hipError_t launch_split(int ne, int model, int per_step, const InstDesc* d0, const BatchHdr* hdr_dev, int cls,
+                        int grid, size_t smem, hipStream_t stream);
+
+// Merge of the tiles of one instance, or of every instance of a batch, down to
+// at most kDirect nodes each (nothing to launch up to kDirect tiles);
+// max_tiles: the most tiles among the instances whose weights are by total
+// cost.
+hipError_t launch_merge(const InstDesc* d0, const BatchHdr* hdr_dev, int max_tiles, int n_inst,
                         hipStream_t stream);
 
 // Combine of the tile rows of one instance (d0, hdr_dev == nullptr) or of

@@ -5,8 +5,7 @@
 // memory the library allocates.
 //
 // Layout of the array for one call (each region 256-byte aligned):
-//   device state (DevState), then the partial-tree tickets from the next
-//   128-byte line (where the iteration kernel looks for them)
+//   device state (DevState)
 //   S      float  [K]
 //   eps    float2 [T][K]
 //   partials      partial_doubles(T, per_step, tiles)
@@ -50,23 +49,18 @@ alignas(256) unsigned char g_stage[64 << 10];  // host staging of one scene
 static_assert(sizeof(g_stage) >= 1024 * 16 + 2048 * 8 + 2 * 2048 * 4 + 1024 * 4 + 256 * 16 + 256,
               "the host staging buffer holds the largest scene");
 
-// Start of an iteration: the iteration counter the Philox counters use, a
-// clean status and zero partial-tree tickets (the tree leaves them at zero
-// after every iteration; a fresh array is cleared here as well).
-__global__ void k_static_begin(DevState* st, unsigned int* tickets, int n_ticket_words,
-                               unsigned long long n_iter)
+// Start of an iteration: the iteration counter the Philox counters use and a
+// clean status.
+__global__ void k_static_begin(DevState* st, unsigned long long n_iter)
 {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        st->n_iter = n_iter;
-        st->reserved = 0;
-        st->status = 0;
-        st->s_min = 0.0;
-        st->z = 0.0;
-        st->log_z = 0.0;
-        st->ess = 0.0;
-    }
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_ticket_words; i += gridDim.x * blockDim.x)
-        tickets[i] = 0u;
+    if (threadIdx.x != 0) return;
+    st->n_iter = n_iter;
+    st->reserved = 0;
+    st->status = 0;
+    st->s_min = 0.0;
+    st->z = 0.0;
+    st->log_z = 0.0;
+    st->ess = 0.0;
 }
 
 // End of an iteration: the statistics of the combine kernel into the
@@ -141,14 +135,13 @@ extern "C" mppi_status mppi_step_static(const mppi_config* cfg, const double x0[
     const SceneLayout lay = scene_layout(n_wp, n_c);
     const int lanes = auto_lanes(*cfg, n_c);
     const int tiles = (K + kBlock / lanes - 1) / (kBlock / lanes);
-    const int n_tickets = combine_tickets(tiles) * kTicketStride;
     size_t off = 0;
     auto carve = [&](size_t bytes) {
         const size_t at = off;
         off = align_up(off + bytes, 256);
         return at;
     };
-    const size_t o_st = carve(state_bytes(tiles));
+    const size_t o_st = carve(sizeof(DevState));
     const size_t o_S = carve(sizeof(float) * (size_t)K);
     const size_t o_eps = carve(sizeof(float2) * (size_t)T * K);
     const size_t o_part =
@@ -180,18 +173,12 @@ extern "C" mppi_status mppi_step_static(const mppi_config* cfg, const double x0[
     HIP_TRY(hipMemcpyAsync(inst.scene, g_stage, lay.bytes, hipMemcpyHostToDevice, stream));
 
     InstDesc d;
-    fill_desc(d, &inst, x0, origin, inst.scene, lay, n_wp, n_c, 0);
-    choose_eps_stage(d, true, stage_allowed(&inst, n_c));  // launched alone, as mppi_step_resident
-    const size_t smem =
-        lds_layout(d.n_wp, d.n_c, d.T, kBlock / d.lanes, d.eps_stage, d.per_step, !d.cull).total;
-    unsigned int* tickets = reinterpret_cast<unsigned int*>(
-        align_up(reinterpret_cast<uintptr_t>(inst.st + 1), 4 * kTicketStride));
-    hipLaunchKernelGGL(k_static_begin, dim3(1), dim3(256), 0, stream, inst.st, tickets, n_tickets,
-                       (unsigned long long)n_iter);
+    fill_desc(d, &inst, x0, origin, inst.scene, lay, n_wp, n_c, 0, true);  // alone, as mppi_step_resident
+    hipLaunchKernelGGL(k_static_begin, dim3(1), dim3(64), 0, stream, inst.st, (unsigned long long)n_iter);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(launch_batch(d.lanes, active_ego(d.n_ego, d.n_c), d.model, d.occ, &d, nullptr, 0,
-                         d.n_tiles,
-                         smem, stream));
+    HIP_TRY(launch_batch(d.lanes, active_ego(d.n_ego, d.n_c), d.model, d.occ, d.per_step, &d, nullptr, 0,
+                         d.n_tiles, iteration_lds(d), stream));
+    if (!d.per_step) HIP_TRY(launch_merge(&d, nullptr, d.n_tiles, 1, stream));
     HIP_TRY(launch_combine(&d, nullptr, combine_groups(d.T), 1, combine_nodes(d.n_tiles, nullptr),
                            stream));
     if (stats) {

@@ -495,3 +495,81 @@ def test_staging_choice_bit_identical(name, lanes):
             outs.append((pl.costs(), pl.noise(), pl.controls(), pl.weights()))
     for a, b in zip(outs[0], outs[1]):
         assert np.array_equal(a, b)
+
+
+def _outputs(mppi, sc, p, occ, iters=2):
+    with mppi.Planner(p, lanes=16) as pl:
+        pl.set_occupancy(occ)
+        for _ in range(iters):
+            pl.step(sc["x0"], sc["waypoints"], sc["circles"])
+        st = pl.stats()
+        out = [pl.costs(), pl.noise(), pl.weights(), pl.controls(),
+               np.array([st["s_min"], st["log_z"], st["ess"]])]
+        if p.get("per_step", 0):
+            out.append(pl.stage_costs())
+        return out
+
+
+def _bent(n, spacing=1.0):
+    """A path that returns beside itself: closest waypoints far apart in index."""
+    s = np.arange(n) * spacing
+    wp = np.zeros((n, 4))
+    wp[:, 0] = 40.0 * np.sin(s / 40.0)
+    wp[:, 1] = 12.0 * np.sin(s / 20.0)
+    if n > 1:
+        wp[:, 2] = np.arctan2(np.gradient(wp[:, 1]), np.gradient(wp[:, 0]))
+    wp[:, 3] = 12.0 + np.sin(s / 15.0)
+    return wp
+
+
+# K, T at the edges of tiles (16 samples), blocks (16 steps) and the ring of
+# blocks, circle counts around 16, 32, 64 (all listed) and past it (collected
+# by block), waypoint counts around one chunk, 64 chunks and past them
+@pytest.mark.parametrize("K,T,n_c,n_wp,over", [
+    (1, 1, 0, 1, {}), (15, 16, 1, 7, {}), (16, 17, 16, 8, {}), (17, 33, 17, 9, {}),
+    (300, 47, 32, 64, dict(per_step=1)), (299, 63, 33, 221, dict(smoothing=1)),
+    (301, 80, 64, 511, dict(w_yaw=50.0, w_target=7.0)), (640, 81, 65, 512, dict(model=1)),
+    (333, 100, 129, 513, dict(collision_only=1)), (200, 150, 400, 1200, dict(d_safe_c=0.4)),
+    (100, 64, 1000, 2048, dict(ego_off=(0.0, 1.0, 2.0, 3.0))),
+    (100, 65, 40, 221, dict(ego_off=(1.0,), d_safe_0=-0.5)), (64, 50, 20, 221, dict(ego_off=())),
+    (100, 300, 30, 221, dict(per_step=1, smoothing=1)), (50, 900, 30, 221, {}),
+    (900, 40, 30, 221, dict(u_min=(0.5, -0.5))), (900, 40, 30, 221, dict(v_max=5.0)),
+])
+def test_split_kernel_bit_identical(K, T, n_c, n_wp, over):
+    """The split iteration kernel (walking, waypoint and circle scans in
+    different waves, the scans by rows) computes the bits of the kernel that
+    does them in one wave."""
+    mppi = _mppi()
+    rng = np.random.Generator(np.random.PCG64(K + T))
+    sc = scenes.tiny(K=K, T=T, n_c=0, seed=3)
+    p = dict(scenes.params(K=K, T=T, dt=0.05, v_max=15.0, seed=7), **over)
+    sc["waypoints"] = _bent(n_wp)
+    sc["circles"] = scenes.sine_circles(rng, n_c, 0.0, 60.0)
+    sc["x0"] = np.array([1.0, 0.5, 0.4, 9.0])
+    _say("split", K, T, n_c, n_wp, over)
+    for a, b in zip(_outputs(mppi, sc, p, -1), _outputs(mppi, sc, p, 0)):
+        assert np.array_equal(a, b, equal_nan=True)
+
+
+@pytest.mark.parametrize("K,lanes", [(32784, 16), (540000, 16), (540000, 8)])
+def test_merge_levels(K, lanes):
+    """Instances just past the combine's 2048 tiles (16 lanes: 2049) and of two
+    merge levels (33750 tiles): the update against the oracle's, in a batch
+    with a small instance as well."""
+    mppi = _mppi()
+    sc = scenes.tiny(K=K, T=4, n_c=5, seed=11)
+    small = scenes.tiny(K=40, T=9, n_c=3, seed=12)
+    p = dict(sc["params"], lam=50.0)
+    _say("merge", K, lanes)
+    with mppi.Planner(p, lanes=lanes) as pl, \
+            mppi.Planner(small["params"], hip_stream=pl.stream()) as other:
+        g = P.gpu_step(pl, sc)
+        S = g["S"]
+        w, _, _ = O.weights(S, p["lam"])
+        assert np.max(np.abs(g["w"] - w)) <= P.W_TOL
+        U = O.update(g["U_prev"], w, g["eps"])
+        assert np.max(np.abs(g["U"] - U) / P.u_tol(U, p["sigma"])) <= 1.0
+        pl.set_state(g["U_prev"], 0)
+        mppi.step_batch([pl, other], np.array([sc["x0"], small["x0"]]),
+                        [(s["waypoints"], s["circles"]) for s in (sc, small)])
+        assert np.array_equal(pl.controls(), g["U"])
