@@ -35,8 +35,8 @@
  *     MPPI_E_INVALID and nothing is written.
  *   - The library owns all device memory and releases it in mppi_destroy.
  *   - Work is enqueued on the handle's HIP stream; calls that return data to
- *     the host synchronize that stream.  A device failure is sticky
- *     (MPPI_E_DEVICE) and makes the handle unusable.
+ *     the host wait until the work enqueued before them is done.  A device
+ *     failure is sticky (MPPI_E_DEVICE) and makes the handle unusable.
  *   - A handle is not thread-safe; distinct handles may be used from distinct
  *     threads.  No C++ exception crosses this interface.
  *   - Arrays are row-major, float64 unless stated otherwise.

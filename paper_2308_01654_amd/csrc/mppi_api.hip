@@ -11,6 +11,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <chrono>
 #include <mutex>
 #include <new>
 #include <string>
@@ -373,6 +374,7 @@ static mppi_status launch_aux(mppi_t* h, F&& f)
 // The pinned, coherent host buffers the device writes results into (U and
 // the state; the optimal trajectory), made on first use so that handles
 // that never read them back -- a server's vehicles -- hold no pinned pages.
+static size_t done_offset(size_t T) { return align_up(sizeof(double) * 2 * T + sizeof(DevState), 64); }
 static mppi_status host_buffers(mppi_t* h)
 {
     if (h->ctl_host) return MPPI_OK;
@@ -381,28 +383,60 @@ static mppi_status host_buffers(mppi_t* h)
     if ((e = hipHostMalloc((void**)&h->traj, sizeof(double) * (5 * (T + 1) + 2 * T),
                            hipHostMallocCoherent)) != hipSuccess ||
         (e = hipHostGetDevicePointer((void**)&h->traj_dev, h->traj, 0)) != hipSuccess ||
-        (e = hipHostMalloc((void**)&h->ctl_host, sizeof(double) * 2 * T + sizeof(DevState),
-                           hipHostMallocCoherent)) != hipSuccess ||
+        (e = hipHostMalloc((void**)&h->ctl_host, done_offset(T) + 64, hipHostMallocCoherent)) !=
+            hipSuccess ||
         (e = hipHostGetDevicePointer((void**)&h->ctl_dev, h->ctl_host, 0)) != hipSuccess) {
         if (h->traj) (void)hipHostFree(h->traj);
         if (h->ctl_host) (void)hipHostFree(h->ctl_host);
         h->traj = h->traj_dev = h->ctl_host = h->ctl_dev = nullptr;
         return fail(MPPI_E_NOMEM, "hipHostMalloc: %s", hipGetErrorString(e));
     }
+    h->done = reinterpret_cast<volatile uint32_t*>(reinterpret_cast<unsigned char*>(h->ctl_host) + done_offset(T));
+    h->done_dev = reinterpret_cast<unsigned*>(reinterpret_cast<unsigned char*>(h->ctl_dev) + done_offset(T));
+    *h->done = h->seq;
     return MPPI_OK;
 }
 
-// The device state after the handle's stream has drained: written by one
-// small kernel into the pinned host buffer, then one synchronisation.
+// Waits until the device has set *flag, a word of pinned host memory, to seq
+// at the end of a kernel of h's stream, by which time everything enqueued
+// before it is done as well.  The word is there 4 us before a synchronisation
+// of the stream would return (11.7 -> 7.7 us for an export from an idle
+// stream); after kSpinUs, or where the word never comes -- a device failure,
+// a stream under capture -- the stream is synchronised, which reports it.
+static mppi_status wait_done(mppi_t* h, const volatile uint32_t* flag, uint32_t seq)
+{
+    constexpr int kSpinUs = 300;
+    const auto t0 = std::chrono::steady_clock::now();
+    for (unsigned i = 1; __atomic_load_n(flag, __ATOMIC_ACQUIRE) != seq; ++i) {
+        __builtin_ia32_pause();
+        if (i % 64 == 0 &&
+            std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(kSpinUs)) {
+            HIP_TRY(hipStreamSynchronize(h->stream));
+            break;
+        }
+    }
+    return MPPI_OK;
+}
+
+// U's first nu values and the device state into the handle's pinned buffer.
+static mppi_status export_results(mppi_t* h, int nu)
+{
+    mppi_status s = host_buffers(h);
+    if (s != MPPI_OK) return s;
+    const uint32_t seq = ++h->seq;
+    HIP_TRY(launch_export_controls(h->U, nu, h->st, h->ctl_dev,
+                                   reinterpret_cast<DevState*>(h->ctl_dev + 2 * h->cfg.T), h->done_dev,
+                                   seq, h->stream));
+    return wait_done(h, h->done, seq);
+}
+
+// The device state after everything enqueued so far: written by one small
+// kernel into the pinned host buffer.
 static mppi_status read_state(mppi_t* h, DevState* out)
 {
-    const mppi_status s = host_buffers(h);
+    const mppi_status s = export_results(h, 0);
     if (s != MPPI_OK) return s;
-    const int nu = 2 * h->cfg.T;
-    DevState* dst = reinterpret_cast<DevState*>(h->ctl_dev + nu);
-    HIP_TRY(launch_export_controls(h->U, 0, h->st, h->ctl_dev, dst, h->stream));
-    HIP_TRY(hipStreamSynchronize(h->stream));
-    *out = *reinterpret_cast<const DevState*>(h->ctl_host + nu);
+    *out = *reinterpret_cast<const DevState*>(h->ctl_host + 2 * h->cfg.T);
     return MPPI_OK;
 }
 
@@ -415,12 +449,20 @@ static mppi_status sync_status(mppi_t* h)
     DevState st;
     const mppi_status s = read_state(h, &st);
     if (s != MPPI_OK) return s;
+    HIP_TRY(hipStreamSynchronize(h->stream));
     if (st.status != 0)
         return fail(MPPI_E_NONFINITE, "every sample cost of the last step was non-finite");
     return MPPI_OK;
 }
 
 // ---- handles ----------------------------------------------------------------------
+
+// The word behind a staging buffer that holds the number of its last upload
+// whose data the device has read.
+static volatile uint32_t* staged_word(mppi_t* h, int i)
+{
+    return reinterpret_cast<volatile uint32_t*>(h->staging[i] + align_up(h->scene_cap, 64));
+}
 
 void handle_release(mppi_t* h)
 {
@@ -447,7 +489,6 @@ void handle_release(mppi_t* h)
     }
     for (int i = 0; i < 2; ++i) {
         if (h->staging[i]) (void)hipHostFree(h->staging[i]);
-        if (h->staged[i]) (void)hipEventDestroy(h->staged[i]);
     }
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
 }
@@ -497,11 +538,12 @@ mppi_status handle_create(const mppi_config* cfg, void* hip_stream, bool with_sc
              (e = hipMalloc((void**)&h->Stk, sizeof(double) * (size_t)T * K)) != hipSuccess))
             return bail(MPPI_E_NOMEM, "hipMalloc", e);
         for (int i = 0; i < 2; ++i) {
-            if ((e = hipHostMalloc((void**)&h->staging[i], h->scene_cap, hipHostMallocDefault)) !=
-                hipSuccess)
+            // the scene, then the word that the device sets once it has read it
+            if ((e = hipHostMalloc((void**)&h->staging[i], align_up(h->scene_cap, 64) + 64,
+                                   hipHostMallocCoherent)) != hipSuccess ||
+                (e = hipHostGetDevicePointer((void**)&h->staging_dev[i], h->staging[i], 0)) != hipSuccess)
                 return bail(MPPI_E_NOMEM, "hipHostMalloc", e);
-            if ((e = hipEventCreateWithFlags(&h->staged[i], hipEventDisableTiming)) != hipSuccess)
-                return bail(MPPI_E_DEVICE, "hipEventCreate", e);
+            *staged_word(h, i) = 0;
         }
         if ((e = hipMemsetAsync(h->S, 0, sizeof(float) * K, h->stream)) != hipSuccess)
             return bail(MPPI_E_DEVICE, "initialise device state", e);
@@ -903,16 +945,13 @@ mppi_status mppi_set_scene(mppi_t* h, const double x0[4], const mppi_scene* sc)
     if (s != MPPI_OK) return s;
     if ((s = validate_scene(h->cfg, x0, sc)) != MPPI_OK) return s;
     const int b = h->cur;
-    if (h->staged_pending[b]) {
-        HIP_TRY(hipEventSynchronize(h->staged[b]));
-        h->staged_pending[b] = false;
-    }
+    if ((s = wait_done(h, staged_word(h, b), h->staged_seq[b])) != MPPI_OK) return s;
     const SceneLayout L = scene_layout(sc->n_waypoints, sc->n_circles);
     const double origin[2] = {x0[0], x0[1]};
     write_scene(h->staging[b], L, h->cfg, origin, sc);
-    HIP_TRY(hipMemcpyAsync(h->scene, h->staging[b], L.bytes, hipMemcpyHostToDevice, h->stream));
-    HIP_TRY(hipEventRecord(h->staged[b], h->stream));
-    h->staged_pending[b] = true;
+    HIP_TRY(launch_stage(h->staging_dev[b], h->scene, L.bytes,
+                         reinterpret_cast<unsigned*>(h->staging_dev[b] + align_up(h->scene_cap, 64)),
+                         ++h->staged_seq[b], h->stream));
     h->cur ^= 1;
     h->has_scene = true;
     h->origin[0] = origin[0];
@@ -998,12 +1037,9 @@ mppi_status mppi_get_controls(mppi_t* h, double* out, size_t n)
     if (!out || n < (size_t)2 * h->cfg.T)
         return fail(MPPI_E_INVALID, "output buffer needs %d doubles", 2 * h->cfg.T);
     // U and the state written by one small kernel straight into pinned host
-    // memory, then one synchronisation (no copies back to wait for)
-    if ((s = host_buffers(h)) != MPPI_OK) return s;
+    // memory (no copies back to wait for)
     const int nu = 2 * h->cfg.T;
-    HIP_TRY(launch_export_controls(h->U, nu, h->st, h->ctl_dev,
-                                   reinterpret_cast<DevState*>(h->ctl_dev + nu), h->stream));
-    HIP_TRY(hipStreamSynchronize(h->stream));
+    if ((s = export_results(h, nu)) != MPPI_OK) return s;
     memcpy(out, h->ctl_host, sizeof(double) * nu);
     if (h->stepped && reinterpret_cast<const DevState*>(h->ctl_host + nu)->status != 0)
         return fail(MPPI_E_NONFINITE, "every sample cost of the last step was non-finite");
@@ -1038,13 +1074,9 @@ mppi_status mppi_get_state(mppi_t* h, double* U, size_t n, uint64_t* n_iter, uin
     if (s != MPPI_OK) return s;
     if (!U || n < (size_t)2 * h->cfg.T)
         return fail(MPPI_E_INVALID, "state buffer needs %d doubles", 2 * h->cfg.T);
-    // U and the state through the pinned export buffer (one small kernel,
-    // one synchronisation)
-    if ((s = host_buffers(h)) != MPPI_OK) return s;
+    // U and the state through the pinned export buffer (one small kernel)
     const int nu = 2 * h->cfg.T;
-    HIP_TRY(launch_export_controls(h->U, nu, h->st, h->ctl_dev,
-                                   reinterpret_cast<DevState*>(h->ctl_dev + nu), h->stream));
-    HIP_TRY(hipStreamSynchronize(h->stream));
+    if ((s = export_results(h, nu)) != MPPI_OK) return s;
     memcpy(U, h->ctl_host, sizeof(double) * nu);
     if (n_iter) *n_iter = reinterpret_cast<const DevState*>(h->ctl_host + nu)->n_iter;
     if (seed) *seed = h->cfg.seed;
@@ -1137,8 +1169,9 @@ mppi_status mppi_get_trajectory(mppi_t* h, double* states, size_t n_states, doub
     // host buffer: no copy back to wait for
     const size_t ns = cols * (T + 1), nu = (size_t)2 * T;
     if ((s = host_buffers(h)) != MPPI_OK) return s;
-    HIP_TRY(launch_trajectory(a, h->U, h->traj_dev, h->traj_dev + ns, h->stream));
-    HIP_TRY(hipStreamSynchronize(h->stream));
+    const uint32_t seq = ++h->seq;
+    HIP_TRY(launch_trajectory(a, h->U, h->traj_dev, h->traj_dev + ns, h->done_dev, seq, h->stream));
+    if ((s = wait_done(h, h->done, seq)) != MPPI_OK) return s;
     if (states) memcpy(states, h->traj, sizeof(double) * ns);
     if (controls) memcpy(controls, h->traj + ns, sizeof(double) * nu);
     return MPPI_OK;

@@ -93,13 +93,18 @@ struct mppi {
     // then the device state (ctl_dev: its device address)
     double* ctl_host = nullptr;
     double* ctl_dev = nullptr;
+    // word of it that the device sets to the number of the export it has
+    // finished, and that number's last value
+    volatile uint32_t* done = nullptr;
+    unsigned* done_dev = nullptr;
+    uint32_t seq = 0;
     mppi_impl::DevState* st = nullptr;
     unsigned char* scene = nullptr;
     size_t scene_cap = 0;
     // pinned scene staging, double-buffered
     unsigned char* staging[2] = {nullptr, nullptr};
-    hipEvent_t staged[2] = {nullptr, nullptr};
-    bool staged_pending[2] = {false, false};
+    unsigned char* staging_dev[2] = {nullptr, nullptr};
+    uint32_t staged_seq[2] = {0, 0};  // number of each buffer's last upload, set at its end when read
     int cur = 0;
     int max_tiles = 0;
     mppi_impl::BatchWs* batch = nullptr;  // created when this handle leads a batch

@@ -330,11 +330,16 @@ struct TrajArgs {
     int model;      // 1: 5-state model, states written with 5 columns
     double dt, wheelbase, a_min, a_max, d_min, d_max, v_max;
 };
-// U [n] and the device state into host memory the device can write (pinned).
+// U [n] and the device state into host memory the device can write (pinned),
+// then seq into *flag there.
 hipError_t launch_export_controls(const double* U, int n, const DevState* st, double* out_u,
-                                  DevState* out_st, hipStream_t stream);
+                                  DevState* out_st, unsigned* flag, unsigned seq, hipStream_t stream);
 hipError_t launch_trajectory(const TrajArgs& a, const double* U, double* states, double* applied,
-                             hipStream_t stream);
+                             unsigned* flag, unsigned seq, hipStream_t stream);
+// `bytes` (a multiple of 16) from pinned host memory (its device address) to
+// device memory, then seq into *flag.
+hipError_t launch_stage(const void* src, void* dst, size_t bytes, unsigned* flag, unsigned seq,
+                        hipStream_t stream);
 hipError_t launch_shift(double* U, int T, int steps, hipStream_t stream);
 hipError_t launch_copy(const float4* src, float4* dst, size_t n16, hipStream_t stream);
 hipError_t launch_debug_philox(uint32_t key0, uint32_t key1, unsigned long long n_iter,

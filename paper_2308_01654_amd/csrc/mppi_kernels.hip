@@ -763,29 +763,83 @@ hipError_t launch_combine(const InstDesc* d0, const BatchHdr* hdr_dev, int group
     return hipGetLastError();
 }
 
-// Exclusive prefix sum (MAX = false) or maximum (MAX = true) over the
-// threads of a workgroup in thread order (float64): shuffles inside a wave,
-// the totals of the earlier waves through LDS (red: kBlock / 64 doubles).
-// Thread 0 gets 0 (sum) or -inf (maximum).
+// Inclusive prefix sum (MAX = false) or maximum (MAX = true) over the lanes of
+// a wave (float64): inside each row of 16 by row shifts, then lane 15 of rows
+// 0 and 2 into the row after each, then lane 31 into rows 2 and 3.
+template <int CTRL, int ROW_MASK, bool MAX>
+__device__ __forceinline__ double scan_stage(double v)
+{
+    const long long id = __builtin_bit_cast(long long, MAX ? -INFINITY : 0.0);
+    const long long b = __builtin_bit_cast(long long, v);
+    const int lo = __builtin_amdgcn_update_dpp((int)id, (int)b, CTRL, ROW_MASK, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(id >> 32), (int)(b >> 32), CTRL, ROW_MASK, 0xf, false);
+    const double u = __builtin_bit_cast(double, ((long long)hi << 32) | (long long)(unsigned)lo);
+    return MAX ? fmax(v, u) : v + u;
+}
 template <bool MAX>
-__device__ __forceinline__ double block_excl(double v, double* red)
+__device__ __forceinline__ double wave_scan(double v)
+{
+    v = scan_stage<0x111, 0xf, MAX>(v);  // row_shr:1
+    v = scan_stage<0x112, 0xf, MAX>(v);
+    v = scan_stage<0x114, 0xf, MAX>(v);
+    v = scan_stage<0x118, 0xf, MAX>(v);
+    v = scan_stage<0x142, 0xa, MAX>(v);  // row_bcast:15
+    return scan_stage<0x143, 0xc, MAX>(v);  // row_bcast:31
+}
+
+// Exclusive prefix sums (MAX = false) or maxima (MAX = true) of N values over
+// the threads of a workgroup in thread order (float64), the scans side by
+// side: inside a wave by lane moves, the totals of the earlier waves through
+// LDS (red: N * kBlock / 64 doubles).  Thread 0 gets 0 (sum) or -inf
+// (maximum).
+template <bool MAX, int N>
+__device__ __forceinline__ void block_excl(double (&v)[N], double* red)
 {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const double id = MAX ? -INFINITY : 0.0;
-    double incl = v;
+    double incl[N];
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const double u = __shfl_up(incl, o, 64);
-        if (lane >= o) incl = MAX ? fmax(incl, u) : incl + u;
+    for (int i = 0; i < N; ++i) incl[i] = wave_scan<MAX>(v[i]);
+    if (blockDim.x > 64) {
+        __syncthreads();  // red is free
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            if (lane == 63) red[i * (kBlock / 64) + wv] = incl[i];
+        __syncthreads();
     }
-    double excl = __shfl_up(incl, 1, 64);
-    if (lane == 0) excl = id;
-    __syncthreads();  // red is free
-    if (lane == 63) red[wv] = incl;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        double excl = __shfl_up(incl[i], 1, 64);
+        if (lane == 0) excl = id;
+        double before = id;
+        for (int w = 0; w < wv; ++w)
+            before = MAX ? fmax(before, red[i * (kBlock / 64) + w]) : before + red[i * (kBlock / 64) + w];
+        v[i] = MAX ? fmax(before, excl) : before + excl;
+    }
+}
+template <bool MAX>
+__device__ __forceinline__ double block_excl(double v, double* red)
+{
+    double a[1] = {v};
+    block_excl<MAX, 1>(a, red);
+    return a[0];
+}
+
+// A store to the host's memory, past every cache of the device (relaxed, system
+// scope).
+__device__ __forceinline__ void st_host(double* p, size_t i, double v)
+{
+    __hip_atomic_store(reinterpret_cast<unsigned long long*>(p) + i, __builtin_bit_cast(unsigned long long, v),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+// Tells the host that a workgroup's results are in its memory: once every
+// thread's stores there (st_host) are acknowledged, the flag.  (A system-scope
+// fence would also write back what the device's L2 holds for others.)
+__device__ __forceinline__ void post_host(unsigned* flag, unsigned seq)
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    double before = id;
-    for (int i = 0; i < wv; ++i) before = MAX ? fmax(before, red[i]) : before + red[i];
-    return MAX ? fmax(before, excl) : before + excl;
+    if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Optimal rollout of Alg. 1 in float64 and world coordinates: from x0,
@@ -799,48 +853,71 @@ __device__ __forceinline__ double block_excl(double v, double* red)
 // (5-state model) and position are prefix sums of their increments.  A start
 // above v_max, or a positive a_min (the braking bound then lifts the speed
 // above v_max whenever the cap falls below it), is walked step by step by one
-// thread.
+// thread.  kP: steps per thread at most (the launch has a step per thread
+// wherever T allows: the tangents, sines and cosines of the unused ones had
+// been most of the kernel, 6.6 us at T = 16 and 100).
+template <int kP>
 __global__ __launch_bounds__(kBlock) void k_trajectory(TrajArgs a, const double* __restrict__ U,
                                                        double* __restrict__ xs,
-                                                       double* __restrict__ us)
+                                                       double* __restrict__ us, unsigned* flag, unsigned seq)
 {
-    __shared__ double red[kBlock / 64];
+    __shared__ double red[2 * (kBlock / 64)];
+    // Up to 256 steps the results are gathered here and leave in one run of
+    // consecutive stores (the states' columns are strided: each value was a bus
+    // write of its own).
+    __shared__ double out[kP == 1 ? 7 * (kBlock + 1) : 1];
     const int cols = a.model ? 5 : 4;  // the 5-state model also writes delta
     const int T = a.T;
+    const int ns = cols * (T + 1);
+    auto put1 = [&](double* p, int at, int i, double v) {
+        if (kP == 1) out[at + i] = v;
+        else p[i] = v;
+    };
+    auto leave = [&]() {
+        __syncthreads();
+        if (kP == 1) {
+            for (int i = threadIdx.x; i < ns; i += blockDim.x) st_host(xs, i, out[i]);
+            for (int i = threadIdx.x; i < 2 * T; i += blockDim.x) st_host(us, i, out[ns + i]);
+        } else {
+            __threadfence_system();
+        }
+        post_host(flag, seq);
+    };
     auto put = [&](int t, double x, double y, double th, double v, double delta) {
-        double* o = xs + (size_t)cols * t;
-        o[0] = x;
-        o[1] = y;
-        o[2] = th;
-        o[3] = v;
-        if (a.model) o[4] = delta;
+        const int o = cols * t;
+        put1(xs, 0, o, x);
+        put1(xs, 0, o + 1, y);
+        put1(xs, 0, o + 2, th);
+        put1(xs, 0, o + 3, v);
+        if (a.model) put1(xs, 0, o + 4, delta);
     };
     if (!(a.x0[3] <= a.v_max) || a.a_min > 0.0) {
-        if (threadIdx.x != 0) return;
-        double x = a.x0[0], y = a.x0[1], th = a.x0[2], v = a.x0[3], delta = a.steer0;
-        put(0, x, y, th, v, delta);
-        for (int t = 0; t < T; ++t) {
-            double acc = fmin(fmax(U[2 * t], a.a_min), a.a_max);
-            acc = fmax(fmin(acc, (a.v_max - v) / a.dt), a.a_min);
-            const double u2 = fmin(fmax(U[2 * t + 1], a.d_min), a.d_max);
-            const double vdt = a.dt * v;
-            const double xn = x + vdt * cos(th);
-            const double yn = y + vdt * sin(th);
-            // the steering angle is the control, or (5-state model) the state
-            const double thn = th + vdt * tan(a.model ? delta : u2) / a.wheelbase;
-            if (a.model) delta += a.dt * u2;
-            v += a.dt * acc;
-            x = xn;
-            y = yn;
-            th = thn;
-            us[2 * t] = acc;
-            us[2 * t + 1] = u2;
-            put(t + 1, x, y, th, v, delta);
+        if (threadIdx.x == 0) {
+            double x = a.x0[0], y = a.x0[1], th = a.x0[2], v = a.x0[3], delta = a.steer0;
+            put(0, x, y, th, v, delta);
+            for (int t = 0; t < T; ++t) {
+                double acc = fmin(fmax(U[2 * t], a.a_min), a.a_max);
+                acc = fmax(fmin(acc, (a.v_max - v) / a.dt), a.a_min);
+                const double u2 = fmin(fmax(U[2 * t + 1], a.d_min), a.d_max);
+                const double vdt = a.dt * v;
+                const double xn = x + vdt * cos(th);
+                const double yn = y + vdt * sin(th);
+                // the steering angle is the control, or (5-state model) the state
+                const double thn = th + vdt * tan(a.model ? delta : u2) / a.wheelbase;
+                if (a.model) delta += a.dt * u2;
+                v += a.dt * acc;
+                x = xn;
+                y = yn;
+                th = thn;
+                put1(us, ns, 2 * t, acc);
+                put1(us, ns, 2 * t + 1, u2);
+                put(t + 1, x, y, th, v, delta);
+            }
         }
+        leave();
         return;
     }
-    constexpr int kP = kMaxT / kBlock;  // steps per thread at most
-    const int P = (T + kBlock - 1) / kBlock;
+    const int P = kP == 1 ? 1 : (T + kBlock - 1) / kBlock;
     const int t0 = threadIdx.x * P;
     double acmd[kP], u2[kP], ds[kP];
     // commanded speed changes and their sums before each own step
@@ -899,14 +976,15 @@ __global__ __launch_bounds__(kBlock) void k_trajectory(TrajArgs a, const double*
             run_y += a.dt * v[j] * sin(th);
         }
     }
-    const double x_before = block_excl<false>(run_x, red);
-    const double y_before = block_excl<false>(run_y, red);
+    double xy_before[2] = {run_x, run_y};
+    block_excl<false, 2>(xy_before, red);
+    const double x_before = xy_before[0], y_before = xy_before[1];
 #pragma unroll
     for (int j = 0; j < kP; ++j) {
         const int t = t0 + j;
         if (j >= P || t >= T) break;
-        us[2 * t] = acc[j];
-        us[2 * t + 1] = u2[j];
+        put1(us, ns, 2 * t, acc[j]);
+        put1(us, ns, 2 * t + 1, u2[j]);
         put(t, a.x0[0] + x_before + dx[j], a.x0[1] + y_before + dy[j], a.x0[2] + th_before + dth[j],
             v[j], a.steer0 + d_before + dd[j]);
         if (t == T - 1) {
@@ -919,6 +997,7 @@ __global__ __launch_bounds__(kBlock) void k_trajectory(TrajArgs a, const double*
                 delta + (a.model ? a.dt * u2[j] : 0.0));
         }
     }
+    leave();
 }
 
 // Iteration kernel for one or many instances of one launch shape (G lanes
@@ -1087,24 +1166,69 @@ __global__ void k_weights(const float* __restrict__ S, const double* __restrict_
 __global__ __launch_bounds__(kBlock) void k_export_controls(const double* __restrict__ U, int n,
                                                             const DevState* __restrict__ st,
                                                             double* __restrict__ out_u,
-                                                            DevState* __restrict__ out_st)
+                                                            DevState* __restrict__ out_st,
+                                                            unsigned* flag, unsigned seq)
 {
-    for (int i = threadIdx.x; i < n; i += kBlock) out_u[i] = U[i];
-    if (threadIdx.x == 0) *out_st = *st;
+    constexpr int kWords = sizeof(DevState) / sizeof(double);
+    static_assert(kWords * sizeof(double) == sizeof(DevState), "whole words");
+    if (threadIdx.x < kWords)
+        st_host(reinterpret_cast<double*>(out_st), threadIdx.x, reinterpret_cast<const double*>(st)[threadIdx.x]);
+    for (int i = threadIdx.x; i < n; i += kBlock) st_host(out_u, i, U[i]);
+    post_host(flag, seq);
 }
 
 hipError_t launch_export_controls(const double* U, int n, const DevState* st, double* out_u,
-                                  DevState* out_st, hipStream_t stream)
+                                  DevState* out_st, unsigned* flag, unsigned seq, hipStream_t stream)
 {
     hipLaunchKernelGGL(k_export_controls, dim3(1), dim3(kBlock), 0, stream, U, n, st, out_u,
-                       out_st);
+                       out_st, flag, seq);
     return hipGetLastError();
 }
 
 hipError_t launch_trajectory(const TrajArgs& a, const double* U, double* states, double* applied,
-                             hipStream_t stream)
+                             unsigned* flag, unsigned seq, hipStream_t stream)
 {
-    hipLaunchKernelGGL(k_trajectory, dim3(1), dim3(kBlock), 0, stream, a, U, states, applied);
+    // a step per thread up to 256 steps, of one wave up to 64
+    const dim3 g(1), b(a.T <= 64 ? 64 : kBlock);
+    if (a.T <= kBlock)
+        hipLaunchKernelGGL(k_trajectory<1>, g, b, 0, stream, a, U, states, applied, flag, seq);
+    else
+        hipLaunchKernelGGL(k_trajectory<kMaxT / kBlock>, g, b, 0, stream, a, U, states, applied, flag, seq);
+    return hipGetLastError();
+}
+
+// A staged scene from the pinned host buffer to the device, read over the bus
+// by one workgroup with every load of a thread in flight; the flag tells the
+// host that the buffer may be filled again.  (Against a copy command and an
+// event: 8.7 -> 4.6 us a scene of 4 KB with the kernel after it, where the
+// event's packet alone held up the queue for 4 us.)
+constexpr int kStageThreads = 1024;
+__global__ __launch_bounds__(kStageThreads) void k_stage(const f4v* __restrict__ src, f4v* __restrict__ dst,
+                                                         int n, unsigned* flag, unsigned seq)
+{
+    for (int i0 = 0; i0 < n; i0 += 4 * kStageThreads) {
+        f4v v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + u * kStageThreads + (int)threadIdx.x;
+            if (i < n) v[u] = as_global(src)[i];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + u * kStageThreads + (int)threadIdx.x;
+            if (i < n) as_global(dst)[i] = v[u];
+        }
+    }
+    // (a thread's stores were issued once its loads had returned)
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+hipError_t launch_stage(const void* src, void* dst, size_t bytes, unsigned* flag, unsigned seq,
+                        hipStream_t stream)
+{
+    hipLaunchKernelGGL(k_stage, dim3(1), dim3(kStageThreads), 0, stream, static_cast<const f4v*>(src),
+                       static_cast<f4v*>(dst), (int)(bytes / 16), flag, seq);
     return hipGetLastError();
 }
 

@@ -202,3 +202,52 @@ def test_smoothing_alone_batched_served_bitwise():
         for vid, i, t in tickets:
             got = srv.wait(t, vid)[0]
             assert np.array_equal(got, ref[vids.index(vid)][i]), ("served", vid, i)
+
+
+@pytest.mark.parametrize("model", [0, 1])
+@pytest.mark.parametrize("T", [1, 15, 16, 17, 32, 63, 64, 65, 128, 256, 257])
+def test_trajectory_at_row_wave_and_workgroup_edges(T, model):
+    """Horizons at the edges of the trajectory kernel's scans (a row of 16
+    lanes, a wave, the 256 threads of one step each): equal to the oracle's
+    optimal rollout, from a start whose speed reaches the cap on the way."""
+    mppi = _mppi()
+    sc = scenes.tiny(K=64, T=T, n_c=2, seed=T)
+    p = dict(sc["params"], v_max=10.5)
+    if model:
+        p = scenes.paper_model5(dict(sc, params=p), steer0=0.02)["params"]
+    rng = np.random.Generator(np.random.PCG64(T))
+    U = np.column_stack([rng.uniform(-1.0, 1.1, T), rng.uniform(-0.1, 0.1, T)])
+    with mppi.Planner(p) as pl:
+        if model:
+            pl.set_steering(0.02)
+        pl.set_controls(U)
+        pl.step(sc["x0"], sc["waypoints"], sc["circles"])
+        xs, us = pl.trajectory()
+        ref_x, ref_u = O.optimal_trajectory(p, sc["x0"], pl.controls())
+    _say("trajectory edges", T, model, float(np.max(np.abs(xs - ref_x))))
+    assert np.max(np.abs(us - ref_u)) <= 1e-12
+    assert np.max(np.abs(xs - ref_x)) <= TRAJ_ABS
+
+
+def test_scenes_staged_without_a_read_between_them():
+    """Steps enqueued one after the other, each with another scene, before
+    anything is read back: more than the two staging buffers hold, sizes from
+    one waypoint to the largest scene.  Every step's outcome is that of a
+    handle that reads back after each."""
+    mppi = _mppi()
+    rng = np.random.Generator(np.random.PCG64(5))
+    sc = scenes.tiny(K=300, T=20, n_c=0, seed=5)
+    steps = []
+    for n_wp, n_c in [(221, 60), (1, 0), (2048, 1024), (9, 3), (700, 64), (64, 17), (221, 1), (8, 1024)]:
+        wp = np.resize(scenes.sine_lane(-20.0, 200.0), (n_wp, 4))
+        steps.append((wp, scenes.sine_circles(rng, n_c)))
+    with mppi.Planner(sc["params"]) as a, mppi.Planner(sc["params"]) as b:
+        for wp, ci in steps:
+            a.step(sc["x0"], wp, ci)
+        for wp, ci in steps:
+            b.step(sc["x0"], wp, ci)
+            b.sync()
+            b.controls()
+        assert np.array_equal(a.controls(), b.controls())
+        assert np.array_equal(a.costs(), b.costs())
+        assert a.stats() == b.stats()
