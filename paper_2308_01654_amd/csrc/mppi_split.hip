@@ -21,14 +21,14 @@
 // others' counts.  A walker waits only for blocks that it wrote before, a
 // scanning wave only for the walker, so every wait ends.
 //
-// What bounds it: VALU issue, at K = 4096 (three waves per SIMD, 21k of 25k
-// cycles of a block's three parts) as at the largest instances; before, the
-// chain's latency.  Iteration by HIP events, k_batch before and this kernel
-// now: K = 1024, T = 50 18.4 -> 12.4 us; Table I shape 12.5 -> 9.9; K = 4096,
-// T = 100 31.8 -> 19.0; sine lane (K = 8192, T = 100) 37.1 -> 26.5; K = 32768
-// 95.8 -> 80; stress instance 3.09 -> 2.26 ms; 256 uneven instances 3.03 ->
-// 2.85 ms.  Candidates by rows instead of by wave (mppi_device.hpp) are 30.4
-// -> 27 of the sine lane's and 152 -> 68 us at K = 4096 in the stress scene.
+// What bounds it: VALU issue, at K = 4096 (three waves per SIMD) as at the
+// largest instances; before, the chain's latency.  Iteration by HIP events,
+// k_batch before and this kernel now: K = 1024, T = 50 18.4 -> 12.3 us; Table I
+// shape 12.5 -> 9.8; K = 4096, T = 100 31.8 -> 17.9; sine lane (K = 8192,
+// T = 100) 37.1 -> 24.8; K = 32768 95.8 -> 75.7; stress instance 3.09 -> 2.23
+// ms; 256 uneven instances 3.03 -> 2.72 ms.  Candidates by rows instead of by
+// wave (mppi_device.hpp) took the sine lane from 30.4 to 27 and K = 4096 in
+// the stress scene from 152 to 68 us.
 //
 // The arithmetic of a step is the same code in both kernels and sums are
 // formed in the same order, so their results are the same bit for bit, and
@@ -301,7 +301,10 @@ __device__ __forceinline__ void split_tile(const InstDesc& d, int tile, unsigned
 
     // Tile partial, as in k_batch: the tile minimum, the float64 weights
     // (lane j < 16 of every wave holds sample j's, so that no second barrier
-    // is needed) and one column (step, control) per thread.
+    // is needed) and one column (step, control) per thread, by as many waves
+    // as there are columns for (all of them: 8% of the kernel's instructions
+    // at T = 100).
+    if (64 * wv >= 2 * T) return;
     const int n_valid = min(kSpb, K - tile * kSpb);
     const float Sk = s.sk[tid & (kSpb - 1)];
     const double m_b = row_min((double)Sk);
