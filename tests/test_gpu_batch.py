@@ -267,3 +267,31 @@ def test_combine_step_group_runs(T):
     finally:
         for q in reversed(pls):
             q.close()
+
+
+@pytest.mark.parametrize("over", [dict(), dict(smoothing=1), dict(per_step=1, smoothing=1)])
+@pytest.mark.parametrize("n,T", [(60, 150), (64, 131), (130, 147)])
+def test_large_batch_combines_several_groups_per_workgroup(n, T, over):
+    """Batches whose combine gives a workgroup two (60 and 64 instances) or
+    four (130) step groups, the last run of groups short: every instance, with
+    circles and without, keeps its alone bits."""
+    mppi = _mppi()
+    _say("groups per workgroup", n, T, over)
+    insts = []
+    for i in range(n):
+        sc = scenes.c2_instance(i, (256 + 8 * (i % 3), T - (i % 7), 0 if i % 5 == 0 else 9))
+        insts.append(dict(sc, params=dict(sc["params"], **over)))
+    lead = mppi.Planner(insts[0]["params"])
+    pls = [lead] + [mppi.Planner(sc["params"], hip_stream=lead.stream()) for sc in insts[1:]]
+    try:
+        mppi.step_batch(pls, np.array([sc["x0"] for sc in insts]),
+                        [(sc["waypoints"], sc["circles"]) for sc in insts])
+        got = [(pl.costs(), pl.controls()) for pl in pls]
+        for i in range(0, n, 9):
+            with mppi.Planner(insts[i]["params"]) as pl:
+                pl.step(insts[i]["x0"], insts[i]["waypoints"], insts[i]["circles"])
+                assert np.array_equal(pl.costs(), got[i][0]), i
+                assert np.array_equal(pl.controls(), got[i][1]), i
+    finally:
+        for pl in reversed(pls):
+            pl.close()
