@@ -98,6 +98,9 @@ struct mppi {
     volatile uint32_t* done = nullptr;
     unsigned* done_dev = nullptr;
     uint32_t seq = 0;
+    // number of the results that the last batch leaves in that buffer, current
+    // until the next call that changes U or the state (0: none)
+    uint32_t mail = 0;
     mppi_impl::DevState* st = nullptr;
     unsigned char* scene = nullptr;
     size_t scene_cap = 0;

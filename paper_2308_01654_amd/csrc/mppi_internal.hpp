@@ -129,6 +129,9 @@ struct InstDesc {
     float steer0;         // its initial steering angle
     float ego_ext;        // max |ego_off|
     int out_slot;         // slot in the gathered results of a batch (-1: none)
+    unsigned mail_seq;    // number of the results that a batch leaves at mail
+    double* mail;         // pinned host buffer (its device address) that receives
+                          // U, the state and mail_seq after a batch; or nullptr
     // device pointers
     const float2* wp_xy;  // [n_wp]
     const float* wp_vref; // [n_wp]
@@ -330,6 +333,14 @@ struct TrajArgs {
     int model;      // 1: 5-state model, states written with 5 columns
     double dt, wheelbase, a_min, a_max, d_min, d_max, v_max;
 };
+// A handle's pinned result buffer: U [T][2], the device state, then (64-byte
+// aligned) the word that holds the number of the last results written.
+inline __host__ __device__ size_t done_offset(int T)
+{
+    return align_up(sizeof(double) * 2 * (size_t)T + sizeof(DevState), 64);
+}
+// Leaves the results of every instance of a batch that has a mail buffer there.
+hipError_t launch_mail(const BatchHdr* hdr_dev, int n_inst, hipStream_t stream);
 // U [n] and the device state into host memory the device can write (pinned),
 // then seq into *flag there.
 hipError_t launch_export_controls(const double* U, int n, const DevState* st, double* out_u,

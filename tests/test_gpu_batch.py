@@ -295,3 +295,64 @@ def test_large_batch_combines_several_groups_per_workgroup(n, T, over):
     finally:
         for pl in reversed(pls):
             pl.close()
+
+
+@pytest.mark.parametrize("n", [15, 16, 40])
+def test_results_after_a_batch_and_after_what_follows_it(n):
+    """From 16 instances on a batch leaves its results in the host's memory.
+    What a read returns right after it, after a second batch, and after each
+    call that changes an instance in between (a shift, new controls, a restored
+    state, a step alone), with trajectories read between them, is what handles
+    that are stepped alone return; an instance whose costs are not finite
+    reports it and keeps its controls."""
+    mppi = _mppi()
+    insts = [scenes.c2_instance(i, (256 + 16 * (i % 4), 20 + i % 9, 5)) for i in range(n)]
+    insts[3]["params"] = dict(insts[3]["params"], w_track=1e300)   # float32 infinity
+    lead = mppi.Planner(insts[0]["params"])
+    pls = [lead] + [mppi.Planner(sc["params"], hip_stream=lead.stream()) for sc in insts[1:]]
+    alone = [mppi.Planner(sc["params"]) for sc in insts]
+    x0s = np.array([sc["x0"] for sc in insts])
+
+    def read(pl):
+        try:
+            U = pl.controls()
+        except mppi.MppiError as e:
+            assert e.status == mppi.E_NONFINITE
+            U = None
+        return U, pl.stats(), pl.get_state()
+
+    def same():
+        for k in range(n):
+            a, b = read(pls[k]), read(alone[k])
+            assert (a[0] is None) == (b[0] is None) == (k == 3), k
+            assert a[0] is None or np.array_equal(a[0], b[0]), k
+            assert repr(a[1]) == repr(b[1]), k
+            assert np.array_equal(a[2][0], b[2][0]) and a[2][1:] == b[2][1:], k
+
+    try:
+        for pl, sc in zip(pls + alone, insts + insts):
+            pl.set_scene(sc["x0"], sc["waypoints"], sc["circles"])
+        for it in range(2):
+            mppi.step_batch(pls, x0s)
+            for pl, x0 in zip(alone, x0s):
+                pl.step_resident(x0)
+            same()
+            assert np.array_equal(pls[1].trajectory()[0], alone[1].trajectory()[0])
+            same()
+        for group in (pls, alone):
+            group[0].shift(1)
+            group[1].set_controls(np.full((insts[1]["params"]["T"], 2), 0.01))
+            group[2].set_state(np.full((insts[2]["params"]["T"], 2), 0.02), 9)
+            group[4].step_resident(x0s[4])
+            group[5].trajectory()
+        for k in (0, 1, 2, 4, 5, 6):
+            assert np.array_equal(pls[k].controls(), alone[k].controls()), k
+            assert np.array_equal(pls[k].get_state()[0], alone[k].get_state()[0]), k
+            assert pls[k].get_state()[1] == alone[k].get_state()[1], k
+        mppi.step_batch(pls, x0s)
+        for pl, x0 in zip(alone, x0s):
+            pl.step_resident(x0)
+        same()
+    finally:
+        for pl in reversed(pls + alone):
+            pl.close()
