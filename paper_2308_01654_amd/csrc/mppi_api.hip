@@ -299,12 +299,28 @@ int auto_occ(const mppi_config& c, int n_c)
     return e ? e->occ : 0;
 }
 
+// Where the split kernel beats k_batch (K, T, circles: k_batch -> split, us):
+// at 16 lanes per sample everywhere measured (1024, 50, 3: 18.1 -> 12.3; 8192,
+// 100, 60: 36.8 -> 24.8; 2560, 16, 3: 12.4 -> 9.5); at 8 as well, by less
+// (16384, 24, 16: 17.3 -> 15.4; 24000, 64, 16: 42.0 -> 35.1; 65536, 100, 48: 158 ->
+// 127; 32768, 50, 60: 44.7 -> 45.3).  At 4 it needs a horizon long enough for
+// the samples to drift apart, and circles (65536, 64, 48: 99 -> 87; 131072, 64,
+// 16: 169 -> 156; but 65536, 40, 16: 52 -> 59 and 131072, 64, 0: 141 -> 146); at
+// 2 a span of 16 steps of a tile leaves no room for a second one, and it takes
+// 1.3 to 2 times as long.
+static bool split_pays(const mppi_config& c, int n_c, int lanes)
+{
+    if (lanes == 16) return true;
+    if (c.per_step_weights) return false;
+    return lanes == 8 || (lanes == 4 && c.T >= 64 && n_c > 0);
+}
+
 int occ_choice(const mppi_t* h, int n_wp, int n_c, int lanes, bool alone)
 {
     const mppi_config& c = h->cfg;
-    if (lanes == 16 && !h->no_cull && h->occ_req < 0) {
-        const size_t lds = split_layout(c.T, n_wp, c.per_step_weights).total;
-        const bool one_each = alone && c.K <= 16 * 256;  // at most a tile per compute unit
+    if (!h->no_cull && h->occ_req < 0 && split_pays(c, n_c, lanes)) {
+        const size_t lds = split_layout(c.T, n_wp, lanes, c.per_step_weights).total;
+        const bool one_each = alone && (long)c.K * lanes <= 256 * 256;  // at most a tile per compute unit
         if (lds <= kSplitLds || (one_each && lds <= kSplitLdsAlone)) return kOccSplit;
     }
     // the other compilations exist for 8 and 16 lanes per sample
@@ -758,7 +774,7 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
         order[i] = i;
         const int occ = occ_choice(hs[i], nw, nc, g, false);
         cls[i] = 50 * occ + 25 * (c.model ? 1 : 0) +
-                 5 * (occ == kOccSplit ? (c.per_step_weights ? 3 : 4) : gi) + active_ego(c.n_ego, nc);
+                 5 * (occ == kOccSplit && c.per_step_weights ? 0 : gi) + active_ego(c.n_ego, nc);
         work[i] = (double)c.T * (73.0 + 6.0 * nw + 7.0 * c.n_ego * nc);
     }
     // The split kernel without the circles waves is launched for instances that
@@ -848,14 +864,18 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
     const int shift_blocks = any_shift ? n_blocks : 0;
     const int gather_blocks = (gather_dev && any_out) ? n_blocks : 0;
     static const int kClassLanes[5] = {1, 2, 4, 8, 16};
+    auto launch_class = [&](int c, int grid) {
+        const int occ = c / 50, li = (c % 25) / 5;
+        const bool ps = occ == kOccSplit && li == 0;  // (the split kernel's class for per-step weights)
+        return launch_batch(ps ? 16 : kClassLanes[li], c % 5, (c % 50) / 25, occ, ps, nullptr, hdr_dev, c, grid,
+                            occ == kOccSplit ? smem_s : smem_b, stream);
+    };
     auto enqueue_device_work = [&](size_t copy_bytes) -> hipError_t {
         hipError_t e = hipMemcpyAsync(ws->arena, host, copy_bytes, hipMemcpyHostToDevice, stream);
         if (e == hipSuccess && shift_blocks) e = launch_shift_batch(hdr_dev, shift_blocks, stream);
         for (int c = 0; c < kLaneClasses && e == hipSuccess; ++c)
             if (grids[c] > 0)
-                e = launch_batch(kClassLanes[(c % 25) / 5], c % 5, (c % 50) / 25, c / 50, (c % 25) / 5 == 3,
-                                 nullptr, hdr_dev, c, grids[c], c / 50 == kOccSplit ? smem_s : smem_b,
-                                 stream);
+                e = launch_class(c, grids[c]);
         if (e == hipSuccess) e = launch_merge(nullptr, hdr_dev, merge_tiles, n_blocks, stream);
         if (e == hipSuccess && combine_g)
             e = launch_combine(nullptr, hdr_dev, combine_g, n_blocks, max_nodes, stream);

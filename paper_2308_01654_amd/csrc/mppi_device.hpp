@@ -1323,6 +1323,107 @@ __device__ __forceinline__ void walk_block(const InstDesc& d, const StepControl&
     if (M5) w.delta += ddel_blk;
 }
 
+// Tile partial (total-cost weights): the tile minimum of the samples' costs,
+// the float64 exponential weights and their sums, and every column's weighted
+// sum of the applied perturbations.  All NT threads call it; Sk is the cost of
+// the sample of the lane's group of G, in the first kBlock threads.  red: 64
+// doubles, omega: [spb], eps: the tile's LDS copy of its perturbations
+// ([2T][spb + 1]) where it has one (staged).
+template <int G, int NT>
+__device__ __forceinline__ void tile_partials(const InstDesc& d, int tile, float Sk, double* red, double* omega,
+                                              const float* eps, bool staged)
+{
+    constexpr int SPB = kBlock / G;
+    const int tid = threadIdx.x;
+    const int T = d.T, K = d.K;
+    const int r = tid % G, grp = tid / G;
+    const int k_base = tile * SPB;
+    const int n_valid = min(SPB, K - k_base);
+    double* part = d.partials + (size_t)tile * partial_stride(T, 0);
+    // wave results through LDS, combined in wave order (two barriers)
+    const int wv = tid >> 6;
+    const bool mine = NT == kBlock || tid < kBlock;  // (uniform in a wave)
+    const bool lane0 = (tid & 63) == 0;
+    if (mine) {
+        const double wmin = wave_min((double)Sk);
+        if (lane0) red[wv] = wmin;
+    }
+    __syncthreads();
+    double m_b = red[0];
+#pragma unroll
+    for (int i = 1; i < kBlock / 64; ++i) m_b = fmin(m_b, red[i]);
+    if (mine) {
+        double om = 0.0;
+        if (r == 0 && isfinite(m_b) && Sk < INFINITY) om = exp(-((double)Sk - m_b) / d.lambda);
+        if (r == 0) omega[grp] = om;
+        const double wz = wave_sum(om);
+        const double wq = wave_sum(om * om);
+        if (lane0) {
+            red[4 + wv] = wz;
+            red[8 + wv] = wq;
+        }
+    }
+    __syncthreads();  // also orders the omega stores
+    double z_b = red[4], q_b = red[8];
+#pragma unroll
+    for (int i = 1; i < kBlock / 64; ++i) {
+        z_b += red[4 + i];
+        q_b += red[8 + i];
+    }
+    // Weighted perturbation sums, one column (step, control) per thread,
+    // the float64 weights (the ones Z_b sums) times the float32
+    // perturbations, summed in float64 in sample order: from
+    // the tile's LDS copy of its perturbations (rows padded by one so
+    // that the lanes of a wave read distinct banks) or, when that copy
+    // does not fit, from global memory, sixteen loads in flight.
+    constexpr int NB = SPB < 16 ? SPB : 16;
+    for (int col = tid; col < 2 * T; col += NT) {
+        if (staged) {
+            const float* e = eps + col * (SPB + 1);
+            double acc = 0.0;
+            // whole tiles: every LDS read issued before the chain of FMAs
+            if (n_valid == SPB) {
+                for (int j0 = 0; j0 < SPB; j0 += NB) {
+                    double om[NB];
+                    float ev[NB];
+#pragma unroll
+                    for (int u = 0; u < NB; ++u) {
+                        om[u] = omega[j0 + u];
+                        ev[u] = e[j0 + u];
+                    }
+#pragma unroll
+                    for (int u = 0; u < NB; ++u) acc = fma(om[u], (double)ev[u], acc);
+                }
+            } else {
+                for (int j = 0; j < n_valid; ++j)
+                    acc = fma(omega[j], (double)e[j], acc);
+            }
+            st_g(part, col, acc);
+            continue;
+        }
+        const int t = col >> 1;
+        const float* e =
+            reinterpret_cast<const float*>(d.eps + (size_t)t * K + k_base) + (col & 1);
+        double acc = 0.0;
+        for (int i0 = 0; i0 < n_valid; i0 += NB) {
+            float ev[NB];
+#pragma unroll
+            for (int u = 0; u < NB; ++u) ev[u] = (i0 + u < n_valid) ? ld_g(e, 2 * (i0 + u)) : 0.0f;
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+                if (i0 + u < n_valid) acc = fma(omega[i0 + u], (double)ev[u], acc);
+        }
+        st_g(part, col, acc);
+    }
+    if (tid == 0) {
+        double* hd = d.partials + partial_heads_offset(T, 0, d.n_tiles) + kHeadDoubles * tile;
+        st_g(hd, 0, m_b);
+        st_g(hd, 1, z_b);
+        st_g(hd, 2, q_b);
+        st_g(hd, 3, 0.0);
+    }
+}
+
 // Per-step weights: the cost-to-go of every sample of the tile in
 // float64, then per step the tile minimum, the shifted exponential
 // sums and the weighted perturbations (one thread per step, samples

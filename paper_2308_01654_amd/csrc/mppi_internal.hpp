@@ -152,7 +152,7 @@ struct InstDesc {
 
 // Iteration kernels (the "occupancy" launch choice): the default compilation
 // of k_batch, the one for kHiOccWaves waves per SIMD (8 and 16 lanes per
-// sample only), and the split kernel (16 lanes per sample, culling on).
+// sample only), and the split kernel (2 to 16 lanes per sample, culling on).
 constexpr int kOccDefault = 0;
 constexpr int kOccHigh = 1;
 constexpr int kOccSplit = 2;
@@ -163,8 +163,8 @@ constexpr int kHiOccWaves = 5;
 // (n_inst + 1 ints) at off_prefix and the descriptors at off_descs.
 // Instances are grouped by kernel variant: class c = 50 * occ + 25 * model +
 // 5 * lane_index + ne (occ the iteration kernel; model 0 or 1 (5-state);
-// lane_index 0..4 for 1, 2, 4, 8, 16 lanes per sample, of the split kernel 4
-// with total-cost and 3 with per-step weights; ne = ego circles that meet
+// lane_index 0..4 for 1, 2, 4, 8, 16 lanes per sample, of the split kernel 0
+// for 16 with per-step weights; ne = ego circles that meet
 // obstacle circles, 0..4) owns instances [cls_begin[c], cls_begin[c+1]).
 constexpr int kLaneClasses = 50 * kOccModes;
 struct BatchHdr {
@@ -240,20 +240,28 @@ inline __host__ __device__ LdsLayout lds_layout(int n_wp, int n_c, int T, int sp
     return L;
 }
 
-// The split iteration kernel (mppi_split.hip): a wave of a group of four
-// samples walks, one scans the waypoints and, with ego circles and obstacles,
-// one the circles; the walker's states pass through a ring of kRing blocks of
-// 16 steps.
-constexpr int kRing = 4;
+// The split iteration kernel (mppi_split.hpp): of each of a tile's four walker
+// waves, one wave scans the waypoints and, with ego circles and obstacles, one
+// the circles; the walker's states pass through a ring of split_ring(G) spans
+// of 16 steps (28 KB of states and costs; at two lanes per sample one span
+// takes 57).
+inline __host__ __device__ constexpr int split_ring(int lanes) { return lanes >= 4 ? lanes / 4 : 1; }
 inline __host__ __device__ constexpr int split_threads(int ne) { return kBlock * (ne > 0 ? 3 : 2); }
+// Two workgroups of the split kernel share a compute unit's 160 KB of LDS.
+// With more it is one, and k_batch's four are the faster again once every
+// unit has a tile.
+constexpr size_t kSplitLds = 80 << 10;
+constexpr size_t kSplitLdsAlone = 160 << 10;
 struct SplitLayout {
-    size_t state, circ, wxy, cost, safe, extra, eps, qs, ss, sk, counts, total;
+    size_t state, circ, wxy, cost, safe, extra, eps, qs, ss, carry, red, sk, counts, total;
+    int staged;  // the tile keeps its perturbations at eps
 };
-inline __host__ __device__ SplitLayout split_layout(int T, int n_wp, int per_step)
+inline __host__ __device__ SplitLayout split_layout(int T, int n_wp, int lanes, int per_step)
 {
     SplitLayout L;
     size_t o = 0;
-    const size_t n = (size_t)kRing * kBlock;  // steps in the ring
+    const int spb = kBlock / lanes;                       // samples per tile
+    const size_t n = (size_t)split_ring(lanes) * 16 * spb;  // steps in the ring
     L.state = o;  o += n * 16;
     L.circ = o;   o += (size_t)(kBlock / 64) * 65 * 32;
     L.wxy = o;    o += (size_t)((n_wp + kChunk - 1) / kChunk) * kChunk * 8;
@@ -262,27 +270,27 @@ inline __host__ __device__ SplitLayout split_layout(int T, int n_wp, int per_ste
     L.extra = o;  o += n * 4;
     // the cost-to-go is formed once the ring is free, and takes its place
     // where it fits
-    const size_t ss = per_step ? (size_t)T * (kBlock / 16 + 1) * 8 : 0;
+    const size_t ss = per_step ? (size_t)T * (spb + 1) * 8 : 0;
     L.ss = ss <= o ? 0 : o;
     o += ss <= o ? 0 : ss;
-    L.eps = o;    o += (size_t)2 * T * (kBlock / 16 + 1) * 4;
-    o = align_up(o, 8);
-    L.qs = o;     o += per_step ? (size_t)T * (kBlock / 16 + 1) * 4 : 0;
-    L.sk = o;     o += kBlock / 16 * 4;
+    L.carry = o;  o += lanes < 16 ? (size_t)spb * 16 : 0;
+    L.red = o;    o += lanes < 16 ? (size_t)(64 + spb) * 8 : 0;
+    L.qs = o;     o += per_step ? align_up((size_t)T * (spb + 1) * 4, 8) : 0;
+    L.sk = o;     o += (size_t)spb * 4;
     L.counts = o; o += 4 * (kBlock / 64) * 4;
+    // below 16 lanes per sample the perturbations are read back from L2 where
+    // their copy would keep a second workgroup off the compute unit
+    const size_t eps = (size_t)2 * T * (spb + 1) * 4;
+    L.staged = lanes == 16 || o + eps <= kSplitLds;
+    L.eps = o;    o += L.staged ? eps : 0;
     L.total = align_up(o, 16);
     return L;
 }
-// Two workgroups of the split kernel share a compute unit's 160 KB of LDS.
-// With more it is one, and k_batch's four are the faster again once every
-// unit has a tile.
-constexpr size_t kSplitLds = 80 << 10;
-constexpr size_t kSplitLdsAlone = 160 << 10;
 
 // Dynamic LDS of the iteration kernel of an instance.
 inline size_t iteration_lds(const InstDesc& d)
 {
-    return d.occ == kOccSplit ? split_layout(d.T, d.n_wp, d.per_step).total
+    return d.occ == kOccSplit ? split_layout(d.T, d.n_wp, d.lanes, d.per_step).total
                               : lds_layout(d.n_wp, d.n_c, d.T, kBlock / d.lanes, d.eps_stage, d.per_step,
                                            !d.cull).total;
 }
@@ -297,9 +305,12 @@ hipError_t launch_batch(int lanes, int ne, int model, int occ, int per_step, con
                         hipStream_t stream);
 
 
-// The split kernel, as launch_batch launches it (mppi_split.hip).
-hipError_t launch_split(int ne, int model, int per_step, const InstDesc* d0, const BatchHdr* hdr_dev, int cls,
-                        int grid, size_t smem, hipStream_t stream);
+// The split kernel, as launch_batch launches it (mppi_split.hip; at 2, 4 and 8
+// lanes per sample mppi_split_wide.hip, total-cost weights only).
+hipError_t launch_split(int lanes, int ne, int model, int per_step, const InstDesc* d0, const BatchHdr* hdr_dev,
+                        int cls, int grid, size_t smem, hipStream_t stream);
+hipError_t launch_split_wide(int lanes, int ne, int model, const InstDesc* d0, const BatchHdr* hdr_dev, int cls,
+                             int grid, size_t smem, hipStream_t stream);
 
 // Merge of the tiles of one instance, or of every instance of a batch, down to
 // at most kDirect nodes each (nothing to launch up to kDirect tiles);

@@ -199,92 +199,11 @@ __device__ __forceinline__ void iteration_tile(const InstDesc& d, int tile, unsi
     // ---------------------------------------------------------------- phase 2
     // the tile's last steps go first
     if (d.wave_prio) __builtin_amdgcn_s_setprio(3);
-    const int n_valid = min(SPB, K - k_base);
     if (d.per_step) {
         per_step_partials<kBlock, SPB>(d, tile, s.eps, s.qs, s.ss, L.eps_staged);
     } else {
-        double* part = d.partials + (size_t)tile * partial_stride(T, 0);
-        // Tile minimum, then the tile's exponential sums: wave results through
-        // LDS, combined in wave order (two barriers).
-        const int wv = tid >> 6;
-        const bool lane0 = (tid & 63) == 0;
-        const double wmin = wave_min((double)Sk);
-        if (lane0) s.red[wv] = wmin;
-        __syncthreads();
-        double m_b = s.red[0];
-#pragma unroll
-        for (int i = 1; i < kBlock / 64; ++i) m_b = fmin(m_b, s.red[i]);
-        double om = 0.0;
-        if (r == 0 && isfinite(m_b) && Sk < INFINITY) om = exp(-((double)Sk - m_b) / d.lambda);
-        if (r == 0) s.omega[grp] = om;
-        const double wz = wave_sum(om);
-        const double wq = wave_sum(om * om);
-        if (lane0) {
-            s.red[4 + wv] = wz;
-            s.red[8 + wv] = wq;
-        }
-        __syncthreads();  // also orders the omega stores
-        double z_b = s.red[4], q_b = s.red[8];
-#pragma unroll
-        for (int i = 1; i < kBlock / 64; ++i) {
-            z_b += s.red[4 + i];
-            q_b += s.red[8 + i];
-        }
-        // Weighted perturbation sums, one column (step, control) per thread,
-        // the float64 weights (the ones Z_b sums) times the float32
-        // perturbations, summed in float64 in sample order: from
-        // the tile's LDS copy of its perturbations (rows padded by one so
-        // that the lanes of a wave read distinct banks) or, when that copy
-        // does not fit, from global memory, sixteen loads in flight.
-        constexpr int NB = SPB < 16 ? SPB : 16;
-        for (int col = tid; col < 2 * T; col += kBlock) {
-            if (L.eps_staged) {
-                const float* e = s.eps + col * (SPB + 1);
-                double acc = 0.0;
-                // whole tiles: every LDS read issued before the chain of FMAs
-                constexpr int NU = SPB < 16 ? SPB : 16;
-                if (n_valid == SPB) {
-                    for (int j0 = 0; j0 < SPB; j0 += NU) {
-                        double om[NU];
-                        float ev[NU];
-#pragma unroll
-                        for (int u = 0; u < NU; ++u) {
-                            om[u] = s.omega[j0 + u];
-                            ev[u] = e[j0 + u];
-                        }
-#pragma unroll
-                        for (int u = 0; u < NU; ++u) acc = fma(om[u], (double)ev[u], acc);
-                    }
-                } else {
-                    for (int j = 0; j < n_valid; ++j)
-                        acc = fma(s.omega[j], (double)e[j], acc);
-                }
-                st_g(part, col, acc);
-                continue;
-            }
-            const int t = col >> 1;
-            const float* e =
-                reinterpret_cast<const float*>(d.eps + (size_t)t * K + k_base) + (col & 1);
-            double acc = 0.0;
-            for (int i0 = 0; i0 < n_valid; i0 += NB) {
-                float ev[NB];
-#pragma unroll
-                for (int u = 0; u < NB; ++u) ev[u] = (i0 + u < n_valid) ? ld_g(e, 2 * (i0 + u)) : 0.0f;
-#pragma unroll
-                for (int u = 0; u < NB; ++u)
-                    if (i0 + u < n_valid) acc = fma(s.omega[i0 + u], (double)ev[u], acc);
-            }
-            st_g(part, col, acc);
-        }
-        if (tid == 0) {
-            double* hd = d.partials + partial_heads_offset(T, 0, d.n_tiles) + kHeadDoubles * tile;
-            st_g(hd, 0, m_b);
-            st_g(hd, 1, z_b);
-            st_g(hd, 2, q_b);
-            st_g(hd, 3, 0.0);
-        }
+        tile_partials<G, kBlock>(d, tile, Sk, s.red, s.omega, s.eps, L.eps_staged);
     }
-
 }
 
 // One level of the merge of an instance with more than kDirect tiles, before
@@ -1129,7 +1048,7 @@ hipError_t launch_batch(int lanes, int ne, int model, int occ, int per_step, con
                         const BatchHdr* hdr_dev, int cls, int grid, size_t smem,
                         hipStream_t stream)
 {
-    if (occ == kOccSplit) return launch_split(ne, model, per_step, d0, hdr_dev, cls, grid, smem, stream);
+    if (occ == kOccSplit) return launch_split(lanes, ne, model, per_step, d0, hdr_dev, cls, grid, smem, stream);
     InstDesc zero;
     memset(&zero, 0, sizeof zero);
     const InstDesc& a = d0 ? *d0 : zero;

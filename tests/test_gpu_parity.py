@@ -497,8 +497,8 @@ def test_staging_choice_bit_identical(name, lanes):
         assert np.array_equal(a, b)
 
 
-def _outputs(mppi, sc, p, occ, iters=2):
-    with mppi.Planner(p, lanes=16) as pl:
+def _outputs(mppi, sc, p, occ, iters=2, lanes=16):
+    with mppi.Planner(p, lanes=lanes) as pl:
         pl.set_occupancy(occ)
         for _ in range(iters):
             pl.step(sc["x0"], sc["waypoints"], sc["circles"])
@@ -549,6 +549,42 @@ def test_split_kernel_bit_identical(K, T, n_c, n_wp, over):
     _say("split", K, T, n_c, n_wp, over)
     for a, b in zip(_outputs(mppi, sc, p, -1), _outputs(mppi, sc, p, 0)):
         assert np.array_equal(a, b, equal_nan=True)
+
+
+# tiles of 32 and 64 samples, spans of 16 steps that blocks of 8 and 4 make up,
+# horizons with a partial block first (even remainder) or last (odd), a partial
+# span, the perturbations kept in LDS or read back
+@pytest.mark.parametrize("lanes,K,T,n_c,over", [
+    (8, 1, 8, 1, {}), (8, 31, 9, 3, {}), (8, 33, 15, 17, {}), (8, 32, 16, 33, dict(smoothing=1)),
+    (8, 65, 17, 64, dict(w_yaw=50.0, w_target=7.0)), (8, 500, 33, 65, dict(model=1)),
+    (8, 500, 100, 0, dict(w_yaw=50.0, w_target=7.0)), (8, 300, 190, 30, {}), (8, 300, 250, 30, {}),
+    (4, 1, 64, 1, {}), (4, 63, 65, 3, {}), (4, 65, 66, 17, dict(w_target=7.0)),
+    (4, 64, 67, 40, dict(model=1, w_target=7.0)), (4, 700, 79, 130, dict(collision_only=1)),
+    (4, 700, 80, 20, dict(smoothing=1, w_yaw=50.0)), (4, 700, 81, 20, dict(v_max=5.0)),
+    (4, 200, 140, 20, {}), (4, 200, 128, 20, dict(ego_off=(1.0,))),
+])
+def test_split_kernel_at_8_and_4_lanes_bit_identical(lanes, K, T, n_c, over):
+    """The split kernel with several blocks of the walk per span computes the
+    bits of the kernel that works in one wave, alone and in a batch."""
+    mppi = _mppi()
+    rng = np.random.Generator(np.random.PCG64(K + T))
+    sc = scenes.tiny(K=K, T=T, n_c=0, seed=3)
+    p = dict(scenes.params(K=K, T=T, dt=0.05, v_max=15.0, seed=7), **over)
+    sc["waypoints"] = _bent(333)
+    sc["circles"] = scenes.sine_circles(rng, n_c, 0.0, 60.0)
+    sc["x0"] = np.array([1.0, 0.5, 0.4, 9.0])
+    _say("split", lanes, K, T, n_c, over)
+    ref = _outputs(mppi, sc, p, 0, lanes=lanes)
+    for a, b in zip(_outputs(mppi, sc, p, -1, lanes=lanes), ref):
+        assert np.array_equal(a, b, equal_nan=True)
+    other = scenes.tiny(K=40, T=9, n_c=3, seed=12)
+    with mppi.Planner(p, lanes=lanes) as pl, \
+            mppi.Planner(other["params"], hip_stream=pl.stream()) as q:
+        for _ in range(2):
+            mppi.step_batch([q, pl], np.array([other["x0"], sc["x0"]]),
+                            [(s["waypoints"], s["circles"]) for s in (other, sc)])
+        assert np.array_equal(pl.costs(), ref[0], equal_nan=True)
+        assert np.array_equal(pl.controls(), ref[3])
 
 
 @pytest.mark.parametrize("K,lanes", [(32784, 16), (540000, 16), (540000, 8)])
