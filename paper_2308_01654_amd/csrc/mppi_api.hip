@@ -131,8 +131,10 @@ SceneLayout scene_layout(int n_wp, int n_c)
     L.o_vr = L.o_xy + align_up((size_t)(n_wp + kChunk - 1) / kChunk * kChunk * 8, 16);
     L.o_yw = L.o_vr + align_up((size_t)n_wp * 4, 16);
     L.o_rr = L.o_yw + align_up((size_t)n_wp * 4, 16);
+    L.o_reach = L.o_rr + align_up((size_t)n_c * 4, 16);
+    L.o_grp = L.o_reach + align_up((size_t)n_c * 4, 16);
     // bounding box of every chunk, then the scene's flags
-    L.o_box = L.o_rr + align_up((size_t)n_c * 4, 16);
+    L.o_box = L.o_grp + (size_t)circle_groups(n_c) * 48;
     L.o_flags = L.o_box + (size_t)(n_wp + kChunk - 1) / kChunk * 16;
     L.bytes = L.o_flags + 16;
     return L;
@@ -189,11 +191,61 @@ void write_scene(unsigned char* dst, const SceneLayout& L, const mppi_config& c,
     flags[1] = j0;
     memcpy(&flags[2], &inv_sp, sizeof inv_sp);
     flags[3] = 0;
-    for (int i = 0; i < sc->n_circles; ++i) {
-        const double* o = sc->circles + 5 * i;
+    // The circles as given, or -- the order is free, a clearance is a minimum --
+    // along the longer axis of their positions, the moving ones last, by a
+    // counting sort.
+    const int n_c = sc->n_circles;
+    float* reach = reinterpret_cast<float*>(dst + L.o_reach);
+    const int n_grp = circle_groups(n_c);
+    uint16_t order[kMaxCircles];
+    if (n_grp) {
+        constexpr int kBuckets = 128;
+        double lo[2] = {INFINITY, INFINITY}, hi[2] = {-INFINITY, -INFINITY};
+        for (int i = 0; i < n_c; ++i)
+            for (int a = 0; a < 2; ++a) {
+                lo[a] = std::min(lo[a], sc->circles[5 * i + a]);
+                hi[a] = std::max(hi[a], sc->circles[5 * i + a]);
+            }
+        const int axis = hi[0] - lo[0] >= hi[1] - lo[1] ? 0 : 1;
+        const double scale = kBuckets / std::max(hi[axis] - lo[axis], 1e-9);
+        auto key = [&](int i) {
+            const double* o = sc->circles + 5 * i;
+            const double k = (o[axis] - lo[axis]) * scale;
+            const int b = k > 0.0 ? (int)std::min(k, kBuckets - 1.0) : 0;
+            return b + (o[3] != 0.0 || o[4] != 0.0 ? kBuckets : 0);
+        };
+        int at[2 * kBuckets + 1] = {};
+        for (int i = 0; i < n_c; ++i) ++at[key(i) + 1];
+        for (int b = 0; b < 2 * kBuckets; ++b) at[b + 1] += at[b];
+        for (int i = 0; i < n_c; ++i) order[at[key(i)]++] = (uint16_t)i;
+    }
+    for (int i = 0; i < n_c; ++i) {
+        const double* o = sc->circles + 5 * (n_grp ? order[i] : i);
         pv[i] = make_float4((float)(o[0] - origin[0]), (float)(o[1] - origin[1]), (float)o[3],
                             (float)o[4]);
         rr[i] = (float)(o[2] + c.ego_r);
+        reach[i] = circle_reach(rr[i], pv[i].z, pv[i].w, (float)c.dt);
+    }
+    float4* grp = reinterpret_cast<float4*>(dst + L.o_grp);
+    for (int g = 0; g < n_grp; ++g) {
+        float4 p = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY), v = p;
+        float most = -INFINITY;
+        bool finite = true;
+        for (int i = g * kCircleGroup; i < std::min((g + 1) * kCircleGroup, n_c); ++i) {
+            const float4 q = pv[i];
+            p = make_float4(fminf(p.x, q.x), fmaxf(p.y, q.x), fminf(p.z, q.y), fmaxf(p.w, q.y));
+            v = make_float4(fminf(v.x, q.z), fmaxf(v.y, q.z), fminf(v.z, q.w), fmaxf(v.w, q.w));
+            most = fmaxf(most, reach[i]);
+            finite = finite && isfinite(q.x) && isfinite(q.y) && isfinite(q.z) && isfinite(q.w);
+        }
+        if (!finite) {  // beyond float32: a group that is near everything
+            p = make_float4(-1e30f, 1e30f, -1e30f, 1e30f);
+            v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            most = INFINITY;
+        }
+        grp[3 * g] = p;
+        grp[3 * g + 1] = v;
+        grp[3 * g + 2] = make_float4(most, 0.0f, 0.0f, 0.0f);
     }
 }
 
@@ -653,6 +705,8 @@ void fill_desc(InstDesc& d, const mppi_t* h, const double x0[4], const double or
     d.wp_box = reinterpret_cast<const float4*>(scene + L.o_box);
     d.scene_flags = reinterpret_cast<const int*>(scene + L.o_flags);
     d.c_rr = reinterpret_cast<const float*>(scene + L.o_rr);
+    d.c_reach = reinterpret_cast<const float*>(scene + L.o_reach);
+    d.c_grp = reinterpret_cast<const float4*>(scene + L.o_grp);
     d.U = h->U;
     d.S = h->S;
     d.eps = h->eps;

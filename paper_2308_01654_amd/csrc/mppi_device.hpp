@@ -895,18 +895,11 @@ __device__ __forceinline__ float path_cost_rows(const InstDesc& d, const float4*
 }
 
 // Circles in LDS for the scan by rows: entry e at 2e is (x, y, vx, vy); the
-// radius follows, then the reach of the circle's centre and rim over a block
-// (circle_reach).  Entry 0 is a circle at infinity.
+// radius follows, then circle_reach.  Entry 0 is a circle at infinity.
 __device__ __forceinline__ void put_circle(float4* list, int e, const float4& p, float rr, float reach)
 {
     list[2 * e] = p;
     list[2 * e + 1] = make_float4(rr, reach, 0.0f, 0.0f);
-}
-// Radius around the circle's centre at the middle of a block of 16 steps that
-// holds the circle throughout it, and a margin above float32 rounding.
-__device__ __forceinline__ float circle_reach(const InstDesc& d, const float4& p, float rr)
-{
-    return rr + 0.01f + 7.5f * d.dt * (1.0f + 1e-5f) * __builtin_amdgcn_sqrtf(fmaf(p.w, p.w, p.z * p.z));
 }
 // A box of ego circle centres as centre and half extent (widened by the
 // rounding of forming them), and the largest distance from a centre at which
@@ -959,25 +952,34 @@ __device__ __forceinline__ float row_circle_scan(const float4* list, int e0, uns
     return d_obj;
 }
 
-// The circles a wave keeps for the scan by rows: of at most 64 all are in the
-// list and lane i of a row tests circles i, i + 16, i + 32 and i + 48 (here);
-// of more, a block's scan lists those near the wave's box first.
+// What a wave keeps for the scan by rows: of at most kListedCircles circles all
+// are in the list, and lane i of a row tests circles i, i + 16, i + 32 and
+// i + 48 (p, reach); of more, lane i keeps group i (p[0] its positions, p[1] its
+// velocities, reach[0]), and every span lists the circles of the near groups
+// that are near the wave's box.
 struct RowCircles {
     float4 p[4];
     float reach[4];
 };
+static_assert(kMaxCircles <= 64 * kCircleGroup && kListedCircles == 64, "a lane for every group");
 __device__ __forceinline__ void row_circles_init(const InstDesc& d, float4* list, RowCircles& rc)
 {
     const int lane = threadIdx.x & 63, r = lane & 15;
     const float4 far = make_float4(INFINITY, INFINITY, 0.0f, 0.0f);
     if (lane == 0) put_circle(list, 0, far, 0.0f, 0.0f);
-    if (d.n_c > 64) return;
+    if (d.n_c > kListedCircles) {
+        const int g = min(lane, circle_groups(d.n_c) - 1);
+        rc.p[0] = ld_g(d.c_grp, 3 * g);
+        rc.p[1] = ld_g(d.c_grp, 3 * g + 1);
+        rc.reach[0] = ld_g(reinterpret_cast<const float*>(d.c_grp + 3 * g + 2), 0);
+        return;
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const int c = r + 16 * i;
         rc.p[i] = c < d.n_c ? ld_g(d.c_pv, c) : far;
         const float rr = c < d.n_c ? ld_g(d.c_rr, c) : 0.0f;
-        rc.reach[i] = circle_reach(d, rc.p[i], rr);
+        rc.reach[i] = c < d.n_c ? ld_g(d.c_reach, c) : 0.0f;
         if (lane < 16) put_circle(list, 1 + c, rc.p[i], rr, rc.reach[i]);
     }
 }
@@ -1014,10 +1016,12 @@ __device__ __forceinline__ float obstacle_cost_rows(const InstDesc& d, float4* l
     row.dsmax = inc ? ds : -INFINITY;
     row_reduce5(row.xlo, row.ylo, row.xhi, row.yhi, row.dsmax);
     const EgoBox rb = ego_box(d, row);
-    const float tau_m = ((float)t0 + 8.5f) * d.dt;
+    // the middle of the span's times (of a span that starts before the horizon
+    // at the earliest its start: within 7.5 steps of every step it has)
+    const float tau_m = fmaxf(((float)t0 + 8.5f) * d.dt, 0.0f);
     const float tau = (float)(t0 + r + 1) * d.dt;
     float d_obj = INFINITY;
-    if (d.n_c <= 64) {
+    if (d.n_c <= kListedCircles) {
         unsigned m[2] = {0u, 0u};
 #pragma unroll
         for (int u = 0; u < 4; ++u)
@@ -1030,8 +1034,9 @@ __device__ __forceinline__ float obstacle_cost_rows(const InstDesc& d, float4* l
         if (d.n_c > 32) d_obj = row_circle_scan<NE>(list, 33, m[1], ex, ey, tau, d_obj);
         return safe_cost(d, ds, d_obj);
     }
-    const EgoBox wb = ego_box(d, wave_box_of_rows({fkey(row.xlo), fkey(row.ylo), fkey(row.xhi),
-                                                   fkey(row.yhi), fkey(row.dsmax)}));
+    const WaveBox wbox = wave_box_of_rows({fkey(row.xlo), fkey(row.ylo), fkey(row.xhi), fkey(row.yhi),
+                                           fkey(row.dsmax)});
+    const EgoBox wb = ego_box(d, wbox);
     int cnt = 0;
     auto flush = [&]() {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -1050,13 +1055,32 @@ __device__ __forceinline__ float obstacle_cost_rows(const InstDesc& d, float4* l
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         cnt = 0;
     };
-    for (int base = 0; base < d.n_c; base += 64) {
-        const int i = min(base + lane, d.n_c - 1);
+    // groups near the wave's box, by lanes (tau_m >= 0: a group's positions lie
+    // between its least with the least velocity and its greatest with the
+    // greatest; the margin is the box's)
+    const float gx = fmaxf(fmaxf(fmaf(tau_m, rc.p[1].x, rc.p[0].x) - (wb.xc + wb.xh),
+                                 (wb.xc - wb.xh) - fmaf(tau_m, rc.p[1].y, rc.p[0].y)), 0.0f);
+    const float gy = fmaxf(fmaxf(fmaf(tau_m, rc.p[1].z, rc.p[0].z) - (wb.yc + wb.yh),
+                                 (wb.yc - wb.yh) - fmaf(tau_m, rc.p[1].w, rc.p[0].w)), 0.0f);
+    const float glim = wb.ds + rc.reach[0];
+    unsigned long long groups =
+        __ballot(lane < circle_groups(d.n_c) && fmaf(gy, gy, gx * gx) < glim * glim);
+    // their circles, four groups at a time
+    while (groups) {
+        int mine = -1;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int g = groups ? (int)__builtin_ctzll(groups) : -1;
+            groups &= groups - 1;
+            mine = (lane >> 4) == u ? g : mine;
+        }
+        const int c = mine * kCircleGroup + r;
+        const bool in = mine >= 0 && c < d.n_c;
+        const int i = in ? c : 0;
         const float4 p = ld_g(d.c_pv, i);
         const float rr = ld_g(d.c_rr, i);
-        const float reach = circle_reach(d, p, rr);
-        const bool n = base + lane < d.n_c &&
-                       circle_near(wb, fmaf(tau_m, p.z, p.x), fmaf(tau_m, p.w, p.y), reach);
+        const float reach = ld_g(d.c_reach, i);
+        const bool n = in && circle_near(wb, fmaf(tau_m, p.z, p.x), fmaf(tau_m, p.w, p.y), reach);
         const unsigned long long b = __ballot(n);
         const int add = __builtin_popcountll(b);
         if (cnt + add > 64) flush();

@@ -47,7 +47,7 @@ struct ProfEvent {
 
 // Offsets of the four scene arrays inside a staged scene block.
 struct SceneLayout {
-    size_t o_pv, o_xy, o_vr, o_yw, o_rr, o_box, o_flags, bytes;
+    size_t o_pv, o_xy, o_vr, o_yw, o_rr, o_reach, o_grp, o_box, o_flags, bytes;
 };
 
 // Per-instance extras of a batched launch: scratch buffers that replace the
@@ -115,7 +115,7 @@ struct mppi {
     bool has_scene = false;
     double origin[2] = {0.0, 0.0};
     int n_wp = 0, n_c = 0;
-    mppi_impl::SceneLayout lay = {0, 0, 0, 0, 0, 0};
+    mppi_impl::SceneLayout lay = {};
     // last step
     bool stepped = false;
     double last_x0[4] = {0.0, 0.0, 0.0, 0.0};

@@ -26,10 +26,10 @@
 // largest instances; before, the chain's latency.  Iteration by HIP events,
 // k_batch before and this kernel now: K = 1024, T = 50 18.4 -> 12.3 us; Table I
 // shape 12.5 -> 9.8; K = 4096, T = 100 31.8 -> 17.9; sine lane (K = 8192,
-// T = 100) 37.1 -> 24.8; K = 32768 95.8 -> 75.7; stress instance 3.09 -> 2.23
+// T = 100) 37.1 -> 24.8; K = 32768 95.8 -> 75.7; stress instance 3.09 -> 1.65
 // ms; 256 uneven instances 3.03 -> 2.72 ms.  Candidates by rows instead of by
 // wave (mppi_device.hpp) took the sine lane from 30.4 to 27 and K = 4096 in
-// the stress scene from 152 to 68 us.
+// the stress scene from 152 to 68 us (with its circles in groups 53).
 //
 // The arithmetic of a step is the same code in both kernels and sums are
 // formed in the same order, so their results are the same bit for bit, and

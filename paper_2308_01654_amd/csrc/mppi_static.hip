@@ -46,7 +46,7 @@ std::mutex g_mu;                               // staging buffer and the table b
 unsigned char* g_dev_ptr[kMaxDevices] = {};    // address of `scratch` per device
 alignas(256) unsigned char g_stage[64 << 10];  // host staging of one scene
 
-static_assert(sizeof(g_stage) >= 1024 * 16 + 2048 * 8 + 2 * 2048 * 4 + 1024 * 4 + 256 * 16 + 256,
+static_assert(sizeof(g_stage) >= 1024 * 16 + 2048 * 8 + 2 * 2048 * 4 + 2 * 1024 * 4 + 64 * 48 + 256 * 16 + 256,
               "the host staging buffer holds the largest scene");
 
 // Start of an iteration: the iteration counter the Philox counters use and a

@@ -587,6 +587,46 @@ def test_split_kernel_at_8_and_4_lanes_bit_identical(lanes, K, T, n_c, over):
         assert np.array_equal(pl.controls(), ref[3])
 
 
+# one circle past the listed ones, whole and short last groups, the most; far
+# from the origin; and positions and velocities beyond float32
+@pytest.mark.parametrize("n_c,what", [(65, ""), (80, ""), (81, ""), (700, ""), (1024, ""), (200, "still"),
+                                      (200, "moving"), (300, "far"), (90, "infinite"), (90, "column")])
+@pytest.mark.parametrize("coll", [0, 1])
+def test_grouped_circles_bit_identical(n_c, what, coll):
+    """Scenes of more circles than are listed at once, staged in groups: the
+    costs of the full scans (no culling), bit for bit."""
+    mppi = _mppi()
+    rng = np.random.Generator(np.random.PCG64(n_c))
+    sc = scenes.tiny(K=200, T=60, n_c=0, seed=3)
+    p = dict(scenes.params(K=200, T=60, dt=0.1, v_max=15.0, seed=7), collision_only=coll)
+    ci = scenes.sine_circles(rng, n_c, -10.0, 90.0)
+    ci[:, 1] += rng.normal(0.0, 6.0, n_c)
+    if what == "still":
+        ci[:, 3:] = 0.0
+    elif what == "moving":
+        ci[:, 3:] = rng.normal(0.0, 8.0, (n_c, 2))
+    elif what == "infinite":
+        ci[5, 3], ci[40, 0], ci[70, 4] = 1e300, 1e300, -1e300
+    elif what == "column":
+        ci[:, 0] = 20.0
+    off = np.array([1e5, -2e5]) if what == "far" else np.zeros(2)
+    x0 = np.array([0.0, 0.5, 0.1, 9.0])
+    x0[:2] += off
+    ci[:, :2] += off
+    wp = np.array(scenes.sine_lane(-20.0, 120.0))
+    wp[:, :2] += off
+    _say("grouped circles", n_c, what, coll)
+    outs = []
+    for cull in (True, False):
+        with mppi.Planner(p, lanes=16) as pl:
+            pl.set_culling(cull)
+            for _ in range(2):
+                pl.step(x0, wp, ci)
+            outs.append((pl.costs(), pl.weights(), pl.controls()))
+    for a, b in zip(*outs):
+        assert np.array_equal(a, b, equal_nan=True)
+
+
 @pytest.mark.parametrize("K,lanes", [(32784, 16), (540000, 16), (540000, 8)])
 def test_merge_levels(K, lanes):
     """Instances just past the combine's 2048 tiles (16 lanes: 2049) and of two
