@@ -162,10 +162,10 @@ void write_scene(unsigned char* dst, const SceneLayout& L, const mppi_config& c,
     for (int c = 0; c * kChunk < sc->n_waypoints; ++c) {
         float4 b = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
         for (int j = c * kChunk; j < std::min((c + 1) * kChunk, (int)sc->n_waypoints); ++j) {
-            b.x = fminf(b.x, xy[j].x);
-            b.y = fmaxf(b.y, xy[j].x);
-            b.z = fminf(b.z, xy[j].y);
-            b.w = fmaxf(b.w, xy[j].y);
+            b.x = std::min(b.x, xy[j].x);
+            b.y = std::max(b.y, xy[j].x);
+            b.z = std::min(b.z, xy[j].y);
+            b.w = std::max(b.w, xy[j].y);
         }
         box[c] = b;
     }
@@ -207,24 +207,26 @@ void write_scene(unsigned char* dst, const SceneLayout& L, const mppi_config& c,
                 hi[a] = std::max(hi[a], sc->circles[5 * i + a]);
             }
         const int axis = hi[0] - lo[0] >= hi[1] - lo[1] ? 0 : 1;
-        const double scale = kBuckets / std::max(hi[axis] - lo[axis], 1e-9);
+        const double scale = (kBuckets - 1.0) / std::max(hi[axis] - lo[axis], 1e-9);
         auto key = [&](int i) {
             const double* o = sc->circles + 5 * i;
-            const double k = (o[axis] - lo[axis]) * scale;
-            const int b = k > 0.0 ? (int)std::min(k, kBuckets - 1.0) : 0;
-            return b + (o[3] != 0.0 || o[4] != 0.0 ? kBuckets : 0);
+            const double k = std::min((o[axis] - lo[axis]) * scale, kBuckets - 1.0);
+            return (k > 0.0 ? (int)k : 0) + (o[3] != 0.0 || o[4] != 0.0 ? kBuckets : 0);
         };
         int at[2 * kBuckets + 1] = {};
-        for (int i = 0; i < n_c; ++i) ++at[key(i) + 1];
+        uint16_t bucket[kMaxCircles];
+        for (int i = 0; i < n_c; ++i) ++at[(bucket[i] = (uint16_t)key(i)) + 1];
         for (int b = 0; b < 2 * kBuckets; ++b) at[b + 1] += at[b];
-        for (int i = 0; i < n_c; ++i) order[at[key(i)]++] = (uint16_t)i;
+        for (int i = 0; i < n_c; ++i) order[at[bucket[i]]++] = (uint16_t)i;
     }
     for (int i = 0; i < n_c; ++i) {
         const double* o = sc->circles + 5 * (n_grp ? order[i] : i);
         pv[i] = make_float4((float)(o[0] - origin[0]), (float)(o[1] - origin[1]), (float)o[3],
                             (float)o[4]);
         rr[i] = (float)(o[2] + c.ego_r);
-        reach[i] = circle_reach(rr[i], pv[i].z, pv[i].w, (float)c.dt);
+        reach[i] = pv[i].z == 0.0f && pv[i].w == 0.0f
+                       ? rr[i] + 0.01f
+                       : circle_reach(rr[i], pv[i].z, pv[i].w, (float)c.dt);
     }
     float4* grp = reinterpret_cast<float4*>(dst + L.o_grp);
     for (int g = 0; g < n_grp; ++g) {
@@ -233,9 +235,9 @@ void write_scene(unsigned char* dst, const SceneLayout& L, const mppi_config& c,
         bool finite = true;
         for (int i = g * kCircleGroup; i < std::min((g + 1) * kCircleGroup, n_c); ++i) {
             const float4 q = pv[i];
-            p = make_float4(fminf(p.x, q.x), fmaxf(p.y, q.x), fminf(p.z, q.y), fmaxf(p.w, q.y));
-            v = make_float4(fminf(v.x, q.z), fmaxf(v.y, q.z), fminf(v.z, q.w), fmaxf(v.w, q.w));
-            most = fmaxf(most, reach[i]);
+            p = make_float4(std::min(p.x, q.x), std::max(p.y, q.x), std::min(p.z, q.y), std::max(p.w, q.y));
+            v = make_float4(std::min(v.x, q.z), std::max(v.y, q.z), std::min(v.z, q.w), std::max(v.w, q.w));
+            most = std::max(most, reach[i]);
             finite = finite && isfinite(q.x) && isfinite(q.y) && isfinite(q.z) && isfinite(q.w);
         }
         if (!finite) {  // beyond float32: a group that is near everything
