@@ -487,11 +487,33 @@ static mppi_status wait_done(mppi_t* h, const volatile uint32_t* flag, uint32_t 
     return MPPI_OK;
 }
 
+// Work that changes U is about to be enqueued.  Under capture it runs when the
+// caller launches the graph, which the handle does not see: from then on no
+// batch leaves the handle's results in the host's memory.
+static void changes_results(mppi_t* h)
+{
+    h->mail = 0;
+    if (h->captured) return;
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(h->stream, &c) != hipSuccess) (void)hipGetLastError();
+    else if (c == hipStreamCaptureStatusNone) return;
+    h->captured = true;
+}
+
 // U's first nu values and the device state into the handle's pinned buffer,
 // unless the batch that set them leaves them there.
 static mppi_status export_results(mppi_t* h, int nu)
 {
-    if (h->mail) return wait_done(h, h->done, h->mail);
+    if (h->mail) {
+        const mppi_status s = wait_done(h, h->done, h->mail);
+        if (s != MPPI_OK) return s;
+        // what the caller has enqueued on the stream since is waited for as well
+        if (hipStreamQuery(h->stream) != hipSuccess) {
+            (void)hipGetLastError();
+            HIP_TRY(hipStreamSynchronize(h->stream));
+        }
+        return MPPI_OK;
+    }
     mppi_status s = host_buffers(h);
     if (s != MPPI_OK) return s;
     const uint32_t seq = ++h->seq;
@@ -882,7 +904,7 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
             descs[j].out_slot = ex->out_slot;
             any_out |= ex->out_slot >= 0;
         }
-        if (mail && host_buffers(hi) == MPPI_OK) {
+        if (mail && !hi->captured && host_buffers(hi) == MPPI_OK) {
             descs[j].mail = hi->ctl_dev;
             descs[j].mail_seq = ++hi->seq;
         }
@@ -1069,7 +1091,7 @@ mppi_status mppi_step_resident(mppi_t* h, const double x0[4])
     if (!x0) return fail(MPPI_E_INVALID, "x0 must not be NULL");
     for (int i = 0; i < 4; ++i)
         if (!isfinite(x0[i])) return fail(MPPI_E_INVALID, "x0[%d] is not finite", i);
-    h->mail = 0;
+    changes_results(h);
     InstDesc d;
     fill_desc(d, h, x0, h->origin, h->scene, h->lay, h->n_wp, h->n_c, 0, true);
     hipEvent_t a = nullptr;
@@ -1166,7 +1188,7 @@ mppi_status mppi_shift(mppi_t* h, int32_t steps)
     if (s != MPPI_OK) return s;
     if (steps < 0) return fail(MPPI_E_INVALID, "steps must be >= 0");
     if (steps == 0) return MPPI_OK;
-    h->mail = 0;
+    changes_results(h);
     return launch_aux(h, [&] { return launch_shift(h->U, h->cfg.T, steps, h->stream); });
 }
 

@@ -101,6 +101,7 @@ struct mppi {
     // number of the results that the last batch leaves in that buffer, current
     // until the next call that changes U or the state (0: none)
     uint32_t mail = 0;
+    bool captured = false;  // a call that changes U has been captured by the caller
     mppi_impl::DevState* st = nullptr;
     unsigned char* scene = nullptr;
     size_t scene_cap = 0;

@@ -356,3 +356,51 @@ def test_results_after_a_batch_and_after_what_follows_it(n):
     finally:
         for pl in reversed(pls + alone):
             pl.close()
+
+
+def test_results_after_a_batch_and_a_replayed_graph():
+    """A step that the caller captured changes a handle's controls each time
+    its graph is launched, which the library does not see: what is read after
+    a batch and after the launches that follow it is what the same steps give
+    one by one."""
+    import ctypes
+
+    from paper_2308_01654_amd.hip_events import HipEvents
+
+    mppi = _mppi()
+    insts = [scenes.c2_instance(i, (256, 20 + i % 9, 5)) for i in range(16)]
+    lead = mppi.Planner(insts[0]["params"])
+    stream = ctypes.c_void_p(lead.stream())
+    pls = [lead] + [mppi.Planner(sc["params"], hip_stream=lead.stream()) for sc in insts[1:]]
+    alone = mppi.Planner(insts[0]["params"])
+    x0s = np.array([sc["x0"] for sc in insts])
+    hip = HipEvents().H
+
+    def ok(status):
+        assert status == 0, status
+
+    try:
+        for pl, sc in zip(pls + [alone], insts + insts[:1]):
+            pl.set_scene(sc["x0"], sc["waypoints"], sc["circles"])
+        mppi.step_batch(pls, x0s)
+        alone.step_resident(x0s[0])
+        assert np.array_equal(lead.controls(), alone.controls())
+        graph, run = ctypes.c_void_p(), ctypes.c_void_p()
+        ok(hip.hipStreamBeginCapture(stream, 1))  # thread local
+        lead.step_resident(x0s[0])
+        ok(hip.hipStreamEndCapture(stream, ctypes.byref(graph)))
+        ok(hip.hipGraphInstantiate(ctypes.byref(run), graph, None, None, ctypes.c_size_t(0)))
+        for _ in range(3):
+            mppi.step_batch(pls, x0s)
+            alone.step_resident(x0s[0])
+            for _ in range(2):
+                ok(hip.hipGraphLaunch(run, stream))
+                ok(hip.hipStreamSynchronize(stream))
+                alone.step_resident(x0s[0])
+                assert np.array_equal(lead.controls(), alone.controls())
+        ok(hip.hipGraphExecDestroy(run))
+        ok(hip.hipGraphDestroy(graph))
+    finally:
+        alone.close()
+        for pl in reversed(pls):
+            pl.close()
