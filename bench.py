@@ -26,7 +26,6 @@ from __future__ import annotations
 
 import argparse
 import ctypes
-import hashlib
 import json
 import os
 import sys
@@ -39,10 +38,10 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 from paper_2308_01654_amd.hip_events import HipEvents, time_steps  # noqa: E402
+from paper_2308_01654_amd.profsum import kernel_source_hash  # noqa: E402
 
 PEAK_FP32_TFLOPS = 157.3      # MI355X published FP32 vector peak
 METRIC = "rollout-steps/s (K=8192,T=100) + p99 replan latency, served vs plain MPPI"
-KERNEL_SRC = os.path.join(ROOT, "paper_2308_01654_amd", "csrc", "mppi_kernels.hip")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_iteration_c1.json")
 
 
@@ -52,11 +51,6 @@ def flops_per_rollout_step(n_wp, n_c, n_ego):
     and the compensated sum; 6 per waypoint; 7 per ego-circle x obstacle-circle
     pair."""
     return 73 + 6 * n_wp + 7 * n_ego * n_c
-
-
-def kernel_source_hash():
-    with open(KERNEL_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
 
 
 def load_traffic(n_launch_units):
@@ -565,7 +559,7 @@ def main(argv=None):
                     traffic=load_traffic(K * T), executed=executed, kernel_trace=kernel_trace,
                     achieved_counts="algorithmic flops of full scans (the kernel culls them "
                                     "exactly; executed holds what the hardware counted)",
-                    kernel="k_batch<G,NE,M5> (sampling, rollouts, costs, tile partials)",
+                    kernel="k_split<G,NE,M5,PS> (sampling, rollouts, costs, tile partials)",
                     kernel_ms=round(kern_ms, 5), iteration_ms=round(iter_ms, 5),
                     combine_ms=round(iter_ms - kern_ms, 5), flops_per_rollout_step=F,
                     lanes_per_sample=st["lanes"])

@@ -1,5 +1,5 @@
 // Device code shared by the two iteration kernels (mppi_kernels.hip, where a
-// wave does every part of its samples' rollouts, and mppi_split.hip, where
+// wave does every part of its samples' rollouts, and mppi_split.hpp, where
 // the parts are given to different waves): memory accesses, the noise, the
 // stage cost and its culling, and wave reductions.
 #pragma once

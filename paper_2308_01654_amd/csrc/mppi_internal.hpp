@@ -157,7 +157,7 @@ struct InstDesc {
 
 // Iteration kernels (the "occupancy" launch choice): the default compilation
 // of k_batch, the one for kHiOccWaves waves per SIMD (8 and 16 lanes per
-// sample only), and the split kernel (2 to 16 lanes per sample, culling on).
+// sample only), and the split kernel (4, 8 and 16 lanes per sample, culling on).
 constexpr int kOccDefault = 0;
 constexpr int kOccHigh = 1;
 constexpr int kOccSplit = 2;
@@ -329,7 +329,7 @@ hipError_t launch_batch(int lanes, int ne, int model, int occ, int per_step, con
                         hipStream_t stream);
 
 
-// The split kernel, as launch_batch launches it (mppi_split.hip; at 2, 4 and 8
+// The split kernel, as launch_batch launches it (mppi_split.hip; at 4 and 8
 // lanes per sample mppi_split_wide.hip, total-cost weights only).
 hipError_t launch_split(int lanes, int ne, int model, int per_step, const InstDesc* d0, const BatchHdr* hdr_dev,
                         int cls, int grid, size_t smem, hipStream_t stream);

@@ -23,8 +23,8 @@
 //            omega_i * eps_eff[t][i] over the tile.
 //
 // Above kDirect tiles a fixed-shape tree (k_merge) merges them until kDirect
-// nodes remain.  mppi_split.hip has another iteration kernel, for 16 lanes
-// per sample, with the same results.
+// nodes remain.  mppi_split.hpp has another iteration kernel, for 16, 8 and
+// 4 lanes per sample, with the same results.
 //
 // The combine kernel (k_combine) merges the node rows in node order with the
 // rescale exp(-(m_b - m)/lambda) and updates U in float64: U_t += N_t / Z

@@ -14,8 +14,8 @@
     The same statistics of the iteration and combine kernels as a record
     (calls, average, minimum and maximum duration in ns).
 
-Every JSON record carries the hash of the kernel source it was taken on;
-bench.py reports a record only while that hash matches the source.
+Every JSON record carries the hash of the kernel sources it was taken on;
+bench.py reports a record only while that hash matches them.
 """
 from __future__ import annotations
 
@@ -28,13 +28,20 @@ import os
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SRC = os.path.join(HERE, "csrc", "mppi_kernels.hip")
+# the sources of the iteration kernels and the combine
+KERNEL_SRCS = [os.path.join(HERE, "csrc", n) for n in (
+    "mppi_device.hpp", "mppi_kernels.hip", "mppi_split.hpp", "mppi_split.hip",
+    "mppi_split_wide.hip")]
+ITERATION = ("k_split", "k_batch")   # the two iteration kernels
 COPY_BYTES = 256 << 20   # bench.py --probe: mppi_bench_copy(256 MiB) reads and writes this
 
 
 def kernel_source_hash() -> str:
-    with open(KERNEL_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for p in KERNEL_SRCS:
+        with open(p, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def _rows(d):
@@ -55,10 +62,10 @@ def _per_dispatch(rows):
     return out
 
 
-def _last(disp, key):
-    ids = [i for i, (n, _) in disp.items() if key in n]
+def _last(disp, *keys):
+    ids = [i for i, (n, _) in disp.items() if any(k in n for k in keys)]
     if not ids:
-        raise KeyError(key)
+        raise KeyError(keys)
     i = max(ids)
     return disp[i][0], dict(disp[i][1])
 
@@ -69,8 +76,8 @@ def traffic(fetch_dir, write_dir, out):
     _, cw = _last(dw, "k_copy")
     fetch_scale = COPY_BYTES / (cf["FETCH_SIZE"] * 1024.0)
     write_scale = COPY_BYTES / (cw["WRITE_SIZE"] * 1024.0)
-    kn, kf = _last(df, "k_batch")
-    _, kw = _last(dw, "k_batch")
+    kn, kf = _last(df, *ITERATION)
+    _, kw = _last(dw, *ITERATION)
     cn, cbf = _last(df, "k_combine")
     _, cbw = _last(dw, "k_combine")
     rec = dict(kernel=kn, kernel_source_sha256_16=kernel_source_hash(),
@@ -82,7 +89,7 @@ def traffic(fetch_dir, write_dir, out):
                combine_write_bytes_per_launch=cbw["WRITE_SIZE"] * 1024.0 * write_scale)
     rec["hbm_bytes_per_launch"] = int(rec["fetch_bytes_per_launch"] + rec["write_bytes_per_launch"])
     rec["counters_kib_per_dispatch"] = {"k_copy": [cf["FETCH_SIZE"], cw["WRITE_SIZE"]],
-                                       "k_batch": [kf["FETCH_SIZE"], kw["WRITE_SIZE"]],
+                                       "iteration": [kf["FETCH_SIZE"], kw["WRITE_SIZE"]],
                                        "k_combine": [cbf["FETCH_SIZE"], cbw["WRITE_SIZE"]]}
     with open(out, "w") as f:
         json.dump(rec, f, indent=1)
@@ -92,7 +99,7 @@ def traffic(fetch_dir, write_dir, out):
 def counters(dirs, out):
     vals, kn = {}, None
     for d in dirs:
-        kn, v = _last(_per_dispatch(_rows(d)), "k_batch")
+        kn, v = _last(_per_dispatch(_rows(d)), *ITERATION)
         vals.update(v)
     rec = dict(kernel=kn, kernel_source_sha256_16=kernel_source_hash(), per_dispatch=vals)
     w = vals.get("SQ_WAVES")
@@ -129,11 +136,11 @@ def _stat_rows(d):
 
 def trace(d, out):
     rec = dict(kernel_source_sha256_16=kernel_source_hash())
-    for key, name in (("k_batch", "iteration"), ("k_combine", "combine")):
+    for keys, name in ((ITERATION, "iteration"), (("k_combine",), "combine")):
         # the row of the kernel that ran most often (the benchmark's launches)
-        rows = [r for r in _stat_rows(d) if key in r["Name"]]
+        rows = [r for r in _stat_rows(d) if any(k in r["Name"] for k in keys)]
         if not rows:
-            raise KeyError(key)
+            raise KeyError(keys)
         r = max(rows, key=lambda x: int(x["Calls"]))
         rec[name] = dict(kernel=r["Name"], calls=int(r["Calls"]),
                          average_ns=float(r["AverageNs"]), min_ns=float(r["MinNs"]),
