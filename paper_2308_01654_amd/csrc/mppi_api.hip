@@ -431,9 +431,16 @@ static mppi_status drain_profile(mppi_t* h)
     return MPPI_OK;
 }
 
+// Work is about to be enqueued for one handle.
+static void mail_behind(mppi_t* h)
+{
+    if (h->mail_behind) h->mail_behind->store(true, std::memory_order_relaxed);
+}
+
 template <typename F>
 static mppi_status launch_aux(mppi_t* h, F&& f)
 {
+    mail_behind(h);
     hipEvent_t a = nullptr;
     mppi_status s = record_launch(h, 1, &a);
     if (s != MPPI_OK) return s;
@@ -493,6 +500,7 @@ static mppi_status wait_done(mppi_t* h, const volatile uint32_t* flag, uint32_t 
 static void changes_results(mppi_t* h)
 {
     h->mail = 0;
+    mail_behind(h);
     if (h->captured) return;
     hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(h->stream, &c) != hipSuccess) (void)hipGetLastError();
@@ -504,10 +512,14 @@ static void changes_results(mppi_t* h)
 // unless the batch that set them leaves them there.
 static mppi_status export_results(mppi_t* h, int nu)
 {
-    if (h->mail) {
+    // What the caller has enqueued on the stream since the batch is waited for as
+    // well.  Asking the stream costs 0.1 us while it is idle and 20 us while a
+    // kernel retires, so behind other work of the batch's handles, which they
+    // know of, an export is the faster way (64 handles, controls and trajectory
+    // of each in turn: 38.4 us a handle with the question, 25.9 this way).
+    if (h->mail && !h->mail_behind->load(std::memory_order_relaxed)) {
         const mppi_status s = wait_done(h, h->done, h->mail);
         if (s != MPPI_OK) return s;
-        // what the caller has enqueued on the stream since is waited for as well
         if (hipStreamQuery(h->stream) != hipSuccess) {
             (void)hipGetLastError();
             HIP_TRY(hipStreamSynchronize(h->stream));
@@ -516,6 +528,7 @@ static mppi_status export_results(mppi_t* h, int nu)
     }
     mppi_status s = host_buffers(h);
     if (s != MPPI_OK) return s;
+    mail_behind(h);
     const uint32_t seq = ++h->seq;
     HIP_TRY(launch_export_controls(h->U, nu, h->st, h->ctl_dev,
                                    reinterpret_cast<DevState*>(h->ctl_dev + 2 * h->cfg.T), h->done_dev,
@@ -1007,13 +1020,20 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
         HIP_TRY(enqueue_device_work(bytes));
     }
     if ((s = record_end(prof, 0, a)) != MPPI_OK) return s;
-    if (mail) HIP_TRY(launch_mail(hdr_dev, n, stream));
+    if (mail) {
+        if (!ws->behind) ws->behind = std::make_shared<std::atomic<bool>>();
+        HIP_TRY(launch_mail(hdr_dev, n, stream));
+        ws->behind->store(false, std::memory_order_relaxed);
+    }
     HIP_TRY(hipEventRecord(ws->done[b], stream));
     ws->pending[b] = true;
     ws->cur ^= 1;
     for (int j = 0; j < n; ++j) {
         hs[order[j]]->stepped = true;
-        if (descs[j].mail) hs[order[j]]->mail = descs[j].mail_seq;
+        if (descs[j].mail) {
+            hs[order[j]]->mail = descs[j].mail_seq;
+            hs[order[j]]->mail_behind = ws->behind;
+        }
         hs[order[j]]->last_lanes = descs[j].lanes;
         memcpy(hs[order[j]]->last_x0, x0s + 4 * order[j], sizeof(double) * 4);
         hs[order[j]]->last_steer0 = hs[order[j]]->steer0;
@@ -1070,6 +1090,7 @@ mppi_status mppi_set_scene(mppi_t* h, const double x0[4], const mppi_scene* sc)
     const SceneLayout L = scene_layout(sc->n_waypoints, sc->n_circles);
     const double origin[2] = {x0[0], x0[1]};
     write_scene(h->staging[b], L, h->cfg, origin, sc);
+    mail_behind(h);
     HIP_TRY(launch_stage(h->staging_dev[b], h->scene, L.bytes,
                          reinterpret_cast<unsigned*>(h->staging_dev[b] + align_up(h->scene_cap, 64)),
                          ++h->staged_seq[b], h->stream));
@@ -1294,6 +1315,7 @@ mppi_status mppi_get_trajectory(mppi_t* h, double* states, size_t n_states, doub
     const size_t ns = cols * (T + 1), nu = (size_t)2 * T;
     if ((s = host_buffers(h)) != MPPI_OK) return s;
     const uint32_t seq = ++h->seq;
+    mail_behind(h);
     HIP_TRY(launch_trajectory(a, h->U, h->traj_dev, h->traj_dev + ns, h->done_dev, seq, h->stream));
     if ((s = wait_done(h, h->done, seq)) != MPPI_OK) return s;
     if (states) memcpy(states, h->traj, sizeof(double) * ns);

@@ -6,6 +6,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -37,6 +39,7 @@ struct BatchWs {
     bool pending[2] = {false, false};
     int cur = 0;
     std::vector<GraphEntry> graphs;
+    std::shared_ptr<std::atomic<bool>> behind;  // mail_behind of its handles
 };
 
 struct ProfEvent {
@@ -101,6 +104,9 @@ struct mppi {
     // number of the results that the last batch leaves in that buffer, current
     // until the next call that changes U or the state (0: none)
     uint32_t mail = 0;
+    // set once a handle of that batch has enqueued more on the stream: a matter
+    // of speed only (export_results)
+    std::shared_ptr<std::atomic<bool>> mail_behind;
     bool captured = false;  // a call that changes U has been captured by the caller
     mppi_impl::DevState* st = nullptr;
     unsigned char* scene = nullptr;
