@@ -649,12 +649,14 @@ __device__ __forceinline__ float path_cost_culled(const InstDesc& d, const WaveB
         return fmaf(gy, gy, gx * gx);
     };
     // A second bound from the lane itself (own): the largest over the lanes
-    // of the wave; lanes without a seed give +inf.
+    // of the wave; lanes without a seed give +inf.  Where every squared distance
+    // is beyond float32 the bound is +inf, which the empty boxes past the last
+    // chunk meet too: their lanes never name a candidate.
     if (n_ch <= 64) {
         float ub_box, ub_own;
         wave_minmax_nonneg(far2(lane_box), own, ub_box, ub_own);
         const float thr = fmaf(fminf(ub_box, ub_own), 1.0f + 1e-5f, 1e-6f);
-        scan_chunks(wp4, 0, __ballot(near2(lane_box) <= thr), x, y, best, bch);
+        scan_chunks(wp4, 0, __ballot(near2(lane_box) <= thr) & (~0ull >> (64 - n_ch)), x, y, best, bch);
     } else {
         const float4 empty = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
         float ub, ub_own;
@@ -666,7 +668,7 @@ __device__ __forceinline__ float path_cost_culled(const InstDesc& d, const WaveB
         scan_chunks(wp4, 0, __ballot(near2(lane_box) <= thr), x, y, best, bch);
         for (int base = 64; base < n_ch; base += 64) {
             const float4 b = base + lane < n_ch ? ld_g(d.wp_box, base + lane) : empty;
-            scan_chunks(wp4, base, __ballot(near2(b) <= thr), x, y, best, bch);
+            scan_chunks(wp4, base, __ballot(base + lane < n_ch && near2(b) <= thr), x, y, best, bch);
         }
     }
     if (best < INFINITY) seed = bch;
@@ -839,6 +841,9 @@ __device__ __forceinline__ float path_cost_rows(const InstDesc& d, const float4*
             take(i, ch < n_ch && near(ld_g(d.wp_box, min(ch, n_ch - 1))));
         }
     }
+    // (the empty boxes past the last chunk are near, too, where the bound is
+    // beyond float32)
+    hi = min(hi, n_ch - 1);
     lo = max(min(lo, hi), 0);
     float best = INFINITY;
     int bch = 0;

@@ -1,0 +1,54 @@
+"""Inputs that are finite as given but whose distances, speeds or weights leave
+the range or the resolution of float32: the culled scans of every iteration
+kernel give what the full scans give."""
+import numpy as np
+import pytest
+
+from paper_2308_01654_amd import scenes
+
+pytestmark = pytest.mark.gpu
+
+
+def _mppi():
+    from paper_2308_01654_amd import mppi
+    mppi.load()
+    return mppi
+
+
+def _say(*a):
+    print("  case:", *a, flush=True)
+
+
+# one chunk, a last chunk that is not the 16th, all 64 that a wave's lanes hold,
+# and past them; where one waypoint is near, all chunks are scanned and it is found
+@pytest.mark.parametrize("n_wp", [1, 70, 512, 700])
+@pytest.mark.parametrize("lanes,occ", [(16, -1), (8, -1), (4, -1), (16, 0), (16, 1), (2, -1), (1, -1)])
+def test_waypoints_whose_squared_distance_is_beyond_float32(lanes, occ, n_wp):
+    """No closest waypoint exists in float32: every cost is non-finite, the step
+    reports it and keeps the controls.  With one waypoint at hand the costs are
+    those of the full scan."""
+    mppi = _mppi()
+    sc = scenes.tiny(K=70, T=64, n_c=5, seed=3)
+    wp = np.zeros((n_wp, 4))
+    wp[:, 0] = np.linspace(1e20, 2e20, n_wp)
+    wp[:, 3] = 10.0
+    near = wp.copy()
+    near[n_wp // 2, :2] = 3.0, 1.0
+    for what, w in (("far", wp), ("near", near)):
+        outs = []
+        for cull in (True, False):
+            _say(lanes, occ, n_wp, what, "culling", cull)
+            # a capacity of just these waypoints: nothing of the handle's lies behind them
+            with mppi.Planner(sc["params"], max_waypoints=n_wp, lanes=lanes) as pl:
+                pl.set_occupancy(occ)
+                pl.set_culling(cull)
+                U = pl.controls()
+                pl.step(sc["x0"], w, sc["circles"])
+                if what == "far":
+                    with pytest.raises(mppi.MppiError) as e:
+                        pl.sync()
+                    assert e.value.status == mppi.E_NONFINITE
+                    assert np.array_equal(pl.get_state()[0], U)
+                outs.append(pl.costs())
+        assert np.array_equal(outs[0], outs[1], equal_nan=True)
+        assert np.all(np.isfinite(outs[0]) == (what == "near"))
