@@ -617,8 +617,10 @@ __device__ __forceinline__ float input_cost(const InstDesc& d, float Ua, float U
 //  * circles: a circle whose centre, swept over the wave's time range, stays
 //    farther than max(d_safe) + r_c + r_ego from the box of the wave's ego
 //    circles cannot make c_safe positive for any lane, so it is skipped.
-// Lanes whose position or safety distance is not finite are left out of the
-// wave box: their own cost is not finite under either scan.  The scene is
+// Lanes whose position is not finite are left out of the wave box: their own
+// cost is not finite under either scan.  A safety distance beyond float32
+// counts as +inf, near which every circle is; one that is not a number costs
+// nothing under either scan.  The scene is
 // read from global memory (wave-uniform candidates through the scalar
 // cache); own is the lane's squared distance to the nearest of three
 // waypoints ahead of its previous closest chunk (+inf without one, 0 for a
@@ -768,9 +770,9 @@ __device__ __forceinline__ unsigned row_bits(unsigned long long b)
 
 // Row reductions of five values, two to their minima and three to their
 // maxima, in every lane of the row.  Written out with the float minimum and
-// maximum (none of the values is NaN): the compiler would quiet every moved
-// value first, and the integer keys of the reductions above cost their way
-// there and back (with the waves without columns leaving early: 6093 -> 5640
+// maximum, which pass over a value that is not a number (the ego centres of a
+// heading beyond float32): the compiler would quiet every moved value first, and
+// the integer keys of the reductions above cost their way there and back (with the waves without columns leaving early: 6093 -> 5640
 // vector instructions per four samples of the sine lane, 26.5 -> 24.8 us an
 // iteration).  Four instructions lie between an instruction and the next
 // that moves its result, as a lane move needs two.
@@ -907,23 +909,27 @@ __device__ __forceinline__ void put_circle(float4* list, int e, const float4& p,
     list[2 * e + 1] = make_float4(rr, reach, 0.0f, 0.0f);
 }
 // A box of ego circle centres as centre and half extent (widened by the
-// rounding of forming them), and the largest distance from a centre at which
-// an obstacle circle counts.
+// rounding of forming them; -inf for a box without centres, which is near
+// nothing), and the largest distance from a centre at which an obstacle circle
+// counts.
 struct EgoBox {
     float xc, yc, xh, yh, ds;
 };
 __device__ __forceinline__ EgoBox ego_box(const InstDesc& d, const WaveBox& b)
 {
     EgoBox o;
-    o.xc = 0.5f * (b.xlo + b.xhi);
+    const bool none = b.xlo > b.xhi;
+    o.xc = none ? 0.0f : 0.5f * (b.xlo + b.xhi);
     o.yc = 0.5f * (b.ylo + b.yhi);
-    o.xh = fmaf(1e-6f, fabsf(b.xlo) + fabsf(b.xhi), 0.5f * (b.xhi - b.xlo));
+    o.xh = none ? -INFINITY : fmaf(1e-6f, fabsf(b.xlo) + fabsf(b.xhi), 0.5f * (b.xhi - b.xlo));
     o.yh = fmaf(1e-6f, fabsf(b.ylo) + fabsf(b.yhi), 0.5f * (b.yhi - b.ylo));
     o.ds = d.coll_only ? 0.0f : b.dsmax;
     return o;
 }
 // Whether a circle (at (ox, oy) at the middle of the block) can come within
-// the largest safety distance of a centre in the box (an empty box: no).
+// the largest safety distance of a centre in the box (an empty box: no; a box
+// whose centres are not numbers or a limit below zero: perhaps yes, which costs
+// a look at the circle and no more).
 __device__ __forceinline__ bool circle_near(const EgoBox& b, float ox, float oy, float reach)
 {
     const float gx = fmaxf(fabsf(ox - b.xc) - b.xh, 0.0f);
@@ -997,7 +1003,7 @@ __device__ __forceinline__ float obstacle_cost_rows(const InstDesc& d, float4* l
 {
     const int lane = threadIdx.x & 63, r = lane & 15;
     const float ds = fmaf(d.d_safe_c, v, d.d_safe_0);
-    const bool inc = act && isfinite(x) && isfinite(y) && isfinite(ds);
+    const bool inc = act && isfinite(x) && isfinite(y);
     const float c = __cosf(th), sn = __sinf(th);
     float ex[NE > 0 ? NE : 1], ey[NE > 0 ? NE : 1];
 #pragma unroll
@@ -1018,7 +1024,7 @@ __device__ __forceinline__ float obstacle_cost_rows(const InstDesc& d, float4* l
     row.ylo = inc ? yl : INFINITY;
     row.xhi = inc ? xh : -INFINITY;
     row.yhi = inc ? yh : -INFINITY;
-    row.dsmax = inc ? ds : -INFINITY;
+    row.dsmax = inc && ds == ds ? ds : -INFINITY;
     row_reduce5(row.xlo, row.ylo, row.xhi, row.yhi, row.dsmax);
     const EgoBox rb = ego_box(d, row);
     // the middle of the span's times (of a span that starts before the horizon
@@ -1052,7 +1058,8 @@ __device__ __forceinline__ float obstacle_cost_rows(const InstDesc& d, float4* l
                 const int e = j + 16 * u + r;
                 const float4* q = list + 2 * (e < cnt ? 1 + e : 0);
                 const float4 p = q[0];
-                const bool n = circle_near(rb, fmaf(tau_m, p.z, p.x), fmaf(tau_m, p.w, p.y), q[1].y);
+                const bool n = e < cnt &&
+                               circle_near(rb, fmaf(tau_m, p.z, p.x), fmaf(tau_m, p.w, p.y), q[1].y);
                 m |= row_bits(__ballot(n)) << (16 * u);
             }
             d_obj = row_circle_scan<NE>(list, 1 + j, m, ex, ey, tau, d_obj);
@@ -1109,8 +1116,8 @@ __device__ __forceinline__ float stage_cost_culled(const InstDesc& d, float own_
                                                    float th, float xp, float yp)
 {
     const float ds = fmaf(d.d_safe_c, v, d.d_safe_0);
-    const bool inc = act && isfinite(x) && isfinite(y) && isfinite(ds);
-    const WaveBox wb = wave_box(inc, x, y, ds);
+    const bool inc = act && isfinite(x) && isfinite(y);
+    const WaveBox wb = wave_box(inc, x, y, ds == ds ? ds : -INFINITY);
     float ext;
     float cost = path_cost_culled(d, wb, inc ? own_d2 : 0.0f, vref0, lc.box, vref_uniform, seed, x,
                                   y, v, input_cost(d, Ua, Ud, ea, ed), th, xp, yp, ext);

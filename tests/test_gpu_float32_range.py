@@ -52,3 +52,38 @@ def test_waypoints_whose_squared_distance_is_beyond_float32(lanes, occ, n_wp):
                 outs.append(pl.costs())
         assert np.array_equal(outs[0], outs[1], equal_nan=True)
         assert np.all(np.isfinite(outs[0]) == (what == "near"))
+
+
+# a safety distance that is +inf in float32 for every state, for those in motion
+# (0 * inf is not a number for the others), and -inf; a start so fast that
+# positions leave float32 along the horizon, and headings before positions do;
+# circles listed at once and in groups, one ego circle and four
+@pytest.mark.parametrize("n_c", [1, 20, 40, 90, 300])
+@pytest.mark.parametrize("name,over", [
+    ("distance", dict(d_safe_0=1e39)), ("per speed", dict(d_safe_c=1e39)),
+    ("negative", dict(d_safe_0=-1e39)), ("both", dict(d_safe_0=1e39, collision_only=1)),
+    ("fast", dict(v_max=1e300)), ("fast, hit", dict(v_max=1e300, collision_only=1)),
+    ("heading", dict(v_max=1e300, wheelbase=4e-39)),
+    ("four", dict(d_safe_0=1e39, ego_off=(0.0, 1.0, 2.0, 3.0)))])
+def test_states_and_safety_distances_beyond_float32(name, over, n_c):
+    """Costs of the culled scans, by wave and by rows, equal the full scans'
+    where the safety distance, the position or the heading is not finite."""
+    mppi = _mppi()
+    rng = np.random.Generator(np.random.PCG64(n_c))
+    sc = scenes.tiny(K=90, T=70, n_c=0, seed=4)
+    p = dict(sc["params"], **over)
+    x0 = np.array(sc["x0"])
+    if "v_max" in over:
+        x0[3] = 3e37 if name != "heading" else 10.0
+    ci = scenes.sine_circles(rng, n_c, 0.0, 60.0)
+    for lanes in (16, 8, 4):
+        outs = []
+        for cull, occ in ((0, -1), (1, -1), (1, 0)):
+            _say(name, n_c, lanes, "culling", cull, "occupancy", occ)
+            with mppi.Planner(p, lanes=lanes) as pl:
+                pl.set_occupancy(occ)
+                pl.set_culling(cull)
+                pl.step(x0, sc["waypoints"], ci)
+                outs.append(pl.costs())
+        for o in outs[1:]:
+            assert np.array_equal(outs[0], o, equal_nan=True), (lanes, outs[0][:4], o[:4])
