@@ -711,7 +711,9 @@ void fill_desc(InstDesc& d, const mppi_t* h, const double x0[4], const double or
     d.w_speed = (float)c.w_speed;
     d.w_effort = (float)c.w_effort;
     d.alpha = (float)((c.gamma - 1.0) / (2.0 * c.gamma));
-    d.w_coll = (float)c.w_coll;
+    // (no obstacle term without ego circles or obstacles: a batch may give the
+    // instance to a kernel that adds it, and beyond float32 times 0 is no number)
+    d.w_coll = active_ego(c.n_ego, n_c) ? (float)c.w_coll : 0.0f;
     d.d_safe_c = (float)c.d_safe_c;
     d.d_safe_0 = (float)c.d_safe_0;
     d.n_ego = c.n_ego;

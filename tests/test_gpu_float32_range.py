@@ -87,3 +87,25 @@ def test_states_and_safety_distances_beyond_float32(name, over, n_c):
                 outs.append(pl.costs())
         for o in outs[1:]:
             assert np.array_equal(outs[0], o, equal_nan=True), (lanes, outs[0][:4], o[:4])
+
+
+@pytest.mark.parametrize("lanes", [16, 8, 4])
+def test_obstacle_weight_beyond_float32_without_obstacles(lanes):
+    """An instance without obstacle circles has no obstacle term whatever its
+    weight, alone and in a batch with instances that have circles."""
+    mppi = _mppi()
+    free = scenes.tiny(K=60, T=70, n_c=0, seed=4)
+    free["params"] = dict(free["params"], w_coll=1e39)
+    other = scenes.tiny(K=60, T=70, n_c=6, seed=5)
+    _say(lanes)
+    with mppi.Planner(free["params"], lanes=lanes) as pl:
+        pl.step(free["x0"], free["waypoints"], free["circles"])
+        alone = pl.costs(), pl.controls()
+    assert np.all(np.isfinite(alone[0]))
+    with mppi.Planner(free["params"], lanes=lanes) as pl, \
+            mppi.Planner(other["params"], lanes=lanes, hip_stream=pl.stream()) as q:
+        mppi.step_batch([pl, q], np.array([free["x0"], other["x0"]]),
+                        [(s["waypoints"], s["circles"]) for s in (free, other)])
+        assert np.array_equal(pl.costs(), alone[0])
+        assert np.array_equal(pl.controls(), alone[1])
+        q.sync()
