@@ -225,7 +225,7 @@ void write_scene(unsigned char* dst, const SceneLayout& L, const mppi_config& c,
                             (float)o[4]);
         rr[i] = (float)(o[2] + c.ego_r);
         reach[i] = pv[i].z == 0.0f && pv[i].w == 0.0f
-                       ? rr[i] + 0.01f
+                       ? circle_margin(rr[i])
                        : circle_reach(rr[i], pv[i].z, pv[i].w, (float)c.dt);
     }
     float4* grp = reinterpret_cast<float4*>(dst + L.o_grp);

@@ -226,10 +226,13 @@ inline __host__ __device__ int circle_groups(int n_c)
     return n_c > kListedCircles ? (n_c + kCircleGroup - 1) / kCircleGroup : 0;
 }
 // Radius around a circle's centre at the middle of a span of 16 steps that holds
-// the circle throughout it, and a margin above float32 rounding.
+// the circle throughout it, above float32 rounding: of the radius, and of the
+// two times, whose difference of 7.5 steps carries up to 2^-23 of the horizon's
+// 2048 (3e-5 of it, whatever the velocity).
+inline __host__ __device__ float circle_margin(float rr) { return rr + 0.01f + 1e-6f * fabsf(rr); }
 inline __host__ __device__ float circle_reach(float rr, float vx, float vy, float dt)
 {
-    return rr + 0.01f + 7.5f * dt * (1.0f + 1e-5f) * sqrtf(vx * vx + vy * vy);
+    return circle_margin(rr) + 7.5f * dt * (1.0f + 1e-4f) * sqrtf(vx * vx + vy * vy);
 }
 
 inline __host__ __device__ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }

@@ -109,3 +109,38 @@ def test_obstacle_weight_beyond_float32_without_obstacles(lanes):
         assert np.array_equal(pl.costs(), alone[0])
         assert np.array_equal(pl.controls(), alone[1])
         q.sync()
+
+
+# (dt, circle speed, radius, step at which it is near, x where it starts): late in
+# long horizons, where the times of steps are coarse in float32, and circles whose
+# radius is
+@pytest.mark.parametrize("dt,v,radius,step,x", [
+    (0.291, 29670.8, 1.0, 1920, -16586301.0), (0.258, 25993.1, 1.0, 1984, -13311842.0),
+    (0.408, 28912.8, 1.0, 1311, -15476910.0), (0.274, 1528.4, 1.0, 1952, -817876.9375),
+    (0.283, 1264.3, 1.0, 1951, -698423.0625), (0.283, 1136.2, 1.0, 1823, -586500.8125),
+    (0.271, 1.9, 2979922.0, 1024, 2979396.5), (0.466, 1.8, 2381847.0, 879, -2382587.5),
+    (0.074, 6.0, 2887852.0, 176, 2887775.75), (0.076, 48.0, 3121625.0, 831, -3124662.5)])
+@pytest.mark.parametrize("n_c", [1, 70])
+def test_circles_at_the_resolution_of_float32(dt, v, radius, step, x, n_c):
+    """A circle that comes just within the safety distance of a standing vehicle
+    at the first or last step of a span of 16 counts as it does in the full
+    scan, listed and in a group."""
+    mppi = _mppi()
+    T = 16 * (step // 16 + 1)
+    p = dict(scenes.params(K=1, T=T, dt=dt, v_max=1.0, seed=1), sigma=(0.0, 0.0), ego_off=(0.0,),
+             ego_r=0.5, d_safe_c=0.0, d_safe_0=2.0, w_track=0.0, w_speed=0.0, w_effort=0.0, w_coll=1.0)
+    wp = np.zeros((3, 4))
+    wp[:, 0] = np.arange(3.0)
+    ci = np.zeros((n_c, 5))
+    ci[:, 0], ci[:, 2] = 1e7, 1.0
+    ci[n_c // 2] = x, 0.0, radius, v, 0.0
+    _say(dt, v, radius, step, x, n_c)
+    got = []
+    for cull, occ in ((False, -1), (True, -1), (True, 0)):
+        with mppi.Planner(p, lanes=8) as pl:
+            pl.set_culling(cull)
+            pl.set_occupancy(occ)
+            pl.step(np.zeros(4), wp, ci)
+            got.append(pl.costs()[0])
+    assert got[0] > 0.0
+    assert got[1] == got[0] and got[2] == got[0], got
