@@ -115,6 +115,7 @@ struct mppi {
     unsigned char* staging[2] = {nullptr, nullptr};
     unsigned char* staging_dev[2] = {nullptr, nullptr};
     uint32_t staged_seq[2] = {0, 0};  // number of each buffer's last upload, set at its end when read
+    unsigned long long staged_capture[2] = {0, 0};  // the caller's capture that last took an upload from each
     int cur = 0;
     int max_tiles = 0;
     mppi_impl::BatchWs* batch = nullptr;  // created when this handle leads a batch

@@ -386,7 +386,7 @@ hipError_t launch_export_controls(const double* U, int n, const DevState* st, do
 hipError_t launch_trajectory(const TrajArgs& a, const double* U, double* states, double* applied,
                              unsigned* flag, unsigned seq, hipStream_t stream);
 // `bytes` (a multiple of 16) from pinned host memory (its device address) to
-// device memory, then seq into *flag.
+// device memory, then seq into *flag (unless flag is nullptr).
 hipError_t launch_stage(const void* src, void* dst, size_t bytes, unsigned* flag, unsigned seq,
                         hipStream_t stream);
 hipError_t launch_shift(double* U, int T, int steps, hipStream_t stream);

@@ -1210,7 +1210,7 @@ __global__ __launch_bounds__(kStageThreads) void k_stage(const f4v* __restrict__
     }
     // (a thread's stores were issued once its loads had returned)
     __syncthreads();
-    if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (flag && threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 hipError_t launch_stage(const void* src, void* dst, size_t bytes, unsigned* flag, unsigned seq,
