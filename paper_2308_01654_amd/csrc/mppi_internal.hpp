@@ -229,10 +229,19 @@ inline __host__ __device__ int circle_groups(int n_c)
 // the circle throughout it, above float32 rounding: of the radius, and of the
 // two times, whose difference of 7.5 steps carries up to 2^-23 of the horizon's
 // 2048 (3e-5 of it, whatever the velocity).
-inline __host__ __device__ float circle_margin(float rr) { return rr + 0.01f + 1e-6f * fabsf(rr); }
-inline __host__ __device__ float circle_reach(float rr, float vx, float vy, float dt)
+template <typename F>  // (floats or vectors of them)
+inline F circle_margin(F rr, F above_zero)  // (above_zero: max(rr, 0))
 {
-    return circle_margin(rr) + 7.5f * dt * (1.0f + 1e-4f) * sqrtf(vx * vx + vy * vy);
+    return rr + 0.01f + 1e-6f * above_zero;
+}
+template <typename F>
+inline F circle_travel(F speed, float dt)
+{
+    return 7.5f * dt * (1.0f + 1e-4f) * speed;
+}
+inline float circle_reach(float rr, float vx, float vy, float dt)
+{
+    return circle_margin(rr, fmaxf(rr, 0.0f)) + circle_travel(sqrtf(vx * vx + vy * vy), dt);
 }
 
 inline __host__ __device__ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
