@@ -4,6 +4,7 @@
 // stage cost and its culling, and wave reductions.
 #pragma once
 
+#include <float.h>
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -601,9 +602,8 @@ __device__ __forceinline__ float input_cost(const InstDesc& d, float Ua, float U
                          0.5f * fmaf(Ua, Ua, Ud * Ud));
 }
 
-// The stage cost of stage_cost comes from two scans, path_cost_culled and
-// obstacle_gap_culled, each restricted to what can matter for this wave (all
-// 64 lanes call them; the lanes in the wave box wb are evaluated).
+// The stage cost of stage_cost, with the two scans restricted to what can
+// matter for this wave (all 64 lanes call it; `act` lanes are evaluated).
 // The result is bit-identical to the full scans:
 //  * waypoints: two bounds on every lane's nearest distance^2 -- the
 //    smallest over chunks of the largest distance^2 between the wave's
@@ -617,25 +617,32 @@ __device__ __forceinline__ float input_cost(const InstDesc& d, float Ua, float U
 //  * circles: a circle whose centre, swept over the wave's time range, stays
 //    farther than max(d_safe) + r_c + r_ego from the box of the wave's ego
 //    circles cannot make c_safe positive for any lane, so it is skipped.
-// Lanes whose position is not finite are left out of the wave box: their own
-// cost is not finite under either scan.  A safety distance beyond float32
-// counts as +inf, near which every circle is; one that is not a number costs
-// nothing under either scan.  The scene is
-// read from global memory (wave-uniform candidates through the scalar
-// cache); own is the lane's squared distance to the nearest of three
-// waypoints ahead of its previous closest chunk (+inf without one, 0 for a
-// lane outside the box), formed by the caller, and vref0 the reference speed
-// of waypoint 0.
-
-// Tracking and speed cost added to the input cost q; ext receives the terms
-// beyond (extra_terms).
-__device__ __forceinline__ float path_cost_culled(const InstDesc& d, const WaveBox& wb, float own,
-                                                  float vref0, const float4& lane_box,
-                                                  bool vref_uniform, int& seed, float x, float y,
-                                                  float v, float q, float th, float xp, float yp,
-                                                  float& ext)
+// Lanes whose position or speed is not finite are left out of the wave box:
+// their own cost is not finite under either scan.  A safety distance beyond
+// float32 counts as +inf, near which every circle is; one that is not a number
+// costs nothing under either scan.  The scene is read from global memory
+// (wave-uniform candidates through the scalar
+// cache); own_d2 is the lane's squared distance to the nearest of three
+// waypoints ahead of its previous closest chunk (+inf without one), formed
+// by the caller, and vref0 the reference speed of waypoint 0.  One function: as
+// two, one for each scan, more of what both keep in scalar registers was spilled
+// (lane reads in the 16-lane kernel 774 against 456; 8192 x 100, 60 circles 37.0
+// -> 34.8 us, 16384 x 600, 12 circles 369 -> 337).
+template <int NE>
+__device__ __forceinline__ float stage_cost_culled(const InstDesc& d, float own_d2,
+                                                   float vref0, const LaneCull& lc,
+                                                   bool vref_uniform, bool act,
+                                                   int& seed, float x, float y,
+                                                   float c, float sn, float v, float Ua, float Ud,
+                                                   float ea, float ed, int t, int t_lo, int t_hi,
+                                                   float th, float xp, float yp)
 {
     const int lane = threadIdx.x & 63;
+    const float ds = fmaf(d.d_safe_c, v, d.d_safe_0);
+    const bool inc = act && isfinite(x) && isfinite(y) && isfinite(v);
+    const WaveBox wb = wave_box(inc, x, y, ds == ds ? ds : -INFINITY);
+
+    // ---- waypoints
     const int n_ch = (d.n_wp + kChunk - 1) / kChunk;
     const const_ptr<float> wp4 = as_const(d.wp_xy);
     float best = INFINITY;
@@ -650,27 +657,30 @@ __device__ __forceinline__ float path_cost_culled(const InstDesc& d, const WaveB
         const float gy = fmaxf(fmaxf(b.z - wb.yhi, wb.ylo - b.w), 0.0f);
         return fmaf(gy, gy, gx * gx);
     };
-    // A second bound from the lane itself (own): the largest over the lanes
-    // of the wave; lanes without a seed give +inf.  Where every squared distance
-    // is beyond float32 the bound is +inf, which the empty boxes past the last
-    // chunk meet too: their lanes never name a candidate.
+    // A second bound from the lane itself: its distance^2 to three waypoints
+    // ahead of the chunk it was closest to at its previous step (seed), the
+    // largest over the lanes of the wave; lanes without a seed give +inf.  The
+    // threshold stays finite where every squared distance is beyond float32, so
+    // that it is never met by the empty boxes past the last chunk (at +inf).
+    auto limit = [](float ub) { return fminf(fmaf(ub, 1.0f + 1e-5f, 1e-6f), FLT_MAX); };
+    const float own = inc ? own_d2 : 0.0f;
     if (n_ch <= 64) {
         float ub_box, ub_own;
-        wave_minmax_nonneg(far2(lane_box), own, ub_box, ub_own);
-        const float thr = fmaf(fminf(ub_box, ub_own), 1.0f + 1e-5f, 1e-6f);
-        scan_chunks(wp4, 0, __ballot(near2(lane_box) <= thr) & (~0ull >> (64 - n_ch)), x, y, best, bch);
+        wave_minmax_nonneg(far2(lc.box), own, ub_box, ub_own);
+        const float thr = limit(fminf(ub_box, ub_own));
+        scan_chunks(wp4, 0, __ballot(near2(lc.box) <= thr), x, y, best, bch);
     } else {
         const float4 empty = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
         float ub, ub_own;
-        wave_minmax_nonneg(far2(lane_box), own, ub, ub_own);
+        wave_minmax_nonneg(far2(lc.box), own, ub, ub_own);
         ub = fminf(ub, ub_own);
         for (int base = 64; base < n_ch; base += 64)
             ub = fminf(ub, wave_min_nonneg(far2(base + lane < n_ch ? ld_g(d.wp_box, base + lane) : empty)));
-        const float thr = fmaf(ub, 1.0f + 1e-5f, 1e-6f);
-        scan_chunks(wp4, 0, __ballot(near2(lane_box) <= thr), x, y, best, bch);
+        const float thr = limit(ub);
+        scan_chunks(wp4, 0, __ballot(near2(lc.box) <= thr), x, y, best, bch);
         for (int base = 64; base < n_ch; base += 64) {
             const float4 b = base + lane < n_ch ? ld_g(d.wp_box, base + lane) : empty;
-            scan_chunks(wp4, base, __ballot(base + lane < n_ch && near2(b) <= thr), x, y, best, bch);
+            scan_chunks(wp4, base, __ballot(near2(b) <= thr), x, y, best, bch);
         }
     }
     if (best < INFINITY) seed = bch;
@@ -679,76 +689,69 @@ __device__ __forceinline__ float path_cost_culled(const InstDesc& d, const WaveB
     const bool need_idx = !vref_uniform || d.w_yaw != 0.0f;
     const int bj = need_idx ? chunk_argmin(d.wp_xy, bch, best, x, y) : 0;
     const float vref = vref_uniform ? vref0 : ld_g(d.wp_vref, bj);
-    ext = extra_terms<true>(d, d.wp_xy, d.wp_yaw, bj, x, y, th, xp, yp);
+    const float ext = extra_terms<true>(d, d.wp_xy, d.wp_yaw, bj, x, y, th, xp, yp);
     const float dv = v - vref;
-    return fmaf(d.w_track, best, fmaf(d.w_speed, dv * dv, q));
-}
+    float cost = fmaf(d.w_track, best, fmaf(d.w_speed, dv * dv, input_cost(d, Ua, Ud, ea, ed)));
 
-// Clearance d_obj between the lane's ego circles (heading cosine c and sine
-// sn) and the obstacle circles at the time of the state reached at step t;
-// t_lo, t_hi: the wave's range of t.
-template <int NE>
-__device__ __forceinline__ float obstacle_gap_culled(const InstDesc& d, const WaveBox& wb,
-                                                     const float4& lane_cpv, float lane_crr,
-                                                     float x, float y, float c, float sn, int t,
-                                                     int t_lo, int t_hi)
-{
-    const int lane = threadIdx.x & 63;
-    float ex[NE > 0 ? NE : 1], ey[NE > 0 ? NE : 1];
+    // ---- obstacle circles
+    if (NE > 0) {
+        float ex[NE > 0 ? NE : 1], ey[NE > 0 ? NE : 1];
 #pragma unroll
-    for (int e = 0; e < NE; ++e) {
-        ex[e] = fmaf(d.ego_off[e], c, x);
-        ey[e] = fmaf(d.ego_off[e], sn, y);
-    }
-    const float exlo = wb.xlo - d.ego_ext, exhi = wb.xhi + d.ego_ext;
-    const float eylo = wb.ylo - d.ego_ext, eyhi = wb.yhi + d.ego_ext;
-    const float tau_lo = (float)(t_lo + 1) * d.dt;
-    const float tau_hi = (float)(t_hi + 1) * d.dt;
-    const float tau = (float)(t + 1) * d.dt;
-    auto close = [&](const float4& p, float rr) {
-        const float xa = fmaf(tau_lo, p.z, p.x), xb = fmaf(tau_hi, p.z, p.x);
-        const float ya = fmaf(tau_lo, p.w, p.y), yb = fmaf(tau_hi, p.w, p.y);
-        const float gx = fmaxf(fmaxf(fminf(xa, xb) - exhi, exlo - fmaxf(xa, xb)), 0.0f);
-        const float gy = fmaxf(fmaxf(fminf(ya, yb) - eyhi, eylo - fmaxf(ya, yb)), 0.0f);
-        // collision-only: only circles that can reach an ego circle matter
-        const float lim = (d.coll_only ? 0.0f : wb.dsmax) + rr + 0.01f;
-        return lim > 0.0f && fmaf(gy, gy, gx * gx) < lim * lim;
-    };
-    const const_ptr<float> cpv = as_const(d.c_pv);
-    const const_ptr<float> crr = as_const(d.c_rr);
-    float d_obj = INFINITY;
-    for (int base = 0; base < d.n_c; base += 64) {
-        bool need;
-        if (base == 0) {
-            need = close(lane_cpv, lane_crr);
-        } else {
-            need = base + lane < d.n_c && close(ld_g(d.c_pv, base + lane), ld_g(d.c_rr, base + lane));
+        for (int e = 0; e < NE; ++e) {
+            ex[e] = fmaf(d.ego_off[e], c, x);
+            ey[e] = fmaf(d.ego_off[e], sn, y);
         }
-        unsigned long long m = __ballot(need);
-        while (m) {
-            // four candidates per round trip, loads issued together; a
-            // short last group repeats its first candidate (the minimum
-            // is unchanged)
-            int idx[4];
-            idx[0] = base + __builtin_ctzll(m);
-            m &= m - 1;
-#pragma unroll
-            for (int u = 1; u < 4; ++u) {
-                idx[u] = m ? base + __builtin_ctzll(m) : idx[0];
+        const float exlo = wb.xlo - d.ego_ext, exhi = wb.xhi + d.ego_ext;
+        const float eylo = wb.ylo - d.ego_ext, eyhi = wb.yhi + d.ego_ext;
+        const float tau_lo = (float)(t_lo + 1) * d.dt;
+        const float tau_hi = (float)(t_hi + 1) * d.dt;
+        const float tau = (float)(t + 1) * d.dt;
+        auto close = [&](const float4& p, float rr) {
+            const float xa = fmaf(tau_lo, p.z, p.x), xb = fmaf(tau_hi, p.z, p.x);
+            const float ya = fmaf(tau_lo, p.w, p.y), yb = fmaf(tau_hi, p.w, p.y);
+            const float gx = fmaxf(fmaxf(fminf(xa, xb) - exhi, exlo - fmaxf(xa, xb)), 0.0f);
+            const float gy = fmaxf(fmaxf(fminf(ya, yb) - eyhi, eylo - fmaxf(ya, yb)), 0.0f);
+            // collision-only: only circles that can reach an ego circle matter
+            const float lim = (d.coll_only ? 0.0f : wb.dsmax) + rr + 0.01f;
+            return lim > 0.0f && fmaf(gy, gy, gx * gx) < lim * lim;
+        };
+        const const_ptr<float> cpv = as_const(d.c_pv);
+        const const_ptr<float> crr = as_const(d.c_rr);
+        float d_obj = INFINITY;
+        for (int base = 0; base < d.n_c; base += 64) {
+            bool need;
+            if (base == 0) {
+                need = close(lc.cpv, lc.crr);
+            } else {
+                need = base + lane < d.n_c && close(ld_g(d.c_pv, base + lane), ld_g(d.c_rr, base + lane));
+            }
+            unsigned long long m = __ballot(need);
+            while (m) {
+                // four candidates per round trip, loads issued together; a
+                // short last group repeats its first candidate (the minimum
+                // is unchanged)
+                int idx[4];
+                idx[0] = base + __builtin_ctzll(m);
                 m &= m - 1;
-            }
-            float4 p[4];
-            float rr[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                p[u] = ld4(cpv, idx[u]);
-                rr[u] = crr[idx[u]];
-            }
+                for (int u = 1; u < 4; ++u) {
+                    idx[u] = m ? base + __builtin_ctzll(m) : idx[0];
+                    m &= m - 1;
+                }
+                float4 p[4];
+                float rr[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) d_obj = fminf(d_obj, circle_gap<NE>(ex, ey, p[u], rr[u], tau));
+                for (int u = 0; u < 4; ++u) {
+                    p[u] = ld4(cpv, idx[u]);
+                    rr[u] = crr[idx[u]];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) d_obj = fminf(d_obj, circle_gap<NE>(ex, ey, p[u], rr[u], tau));
+            }
         }
+        cost = fmaf(d.w_coll, safe_cost(d, ds, d_obj), cost);
     }
-    return d_obj;
+    return cost + ext;
 }
 
 // ----------------------------------------------------------------------------
@@ -793,7 +796,7 @@ __device__ __forceinline__ void row_reduce5(float& a, float& b, float& c, float&
 #undef MPPI_STAGE
 }
 
-// Tracking and speed cost added to the input cost q, as path_cost_culled.
+// Tracking and speed cost added to the input cost q, as stage_cost_culled.
 // wxy: the waypoints in LDS, padded to whole chunks with points at infinity;
 // box[i]: chunk (lane mod 16) + 16 i (instances of at most 64 chunks);
 // (xg, yg) and base: the position at the lane's previous step and the
@@ -1103,30 +1106,6 @@ __device__ __forceinline__ float obstacle_cost_rows(const InstDesc& d, float4* l
     }
     flush();
     return safe_cost(d, ds, d_obj);
-}
-
-// The stage cost with both scans culled, in one wave.
-template <int NE>
-__device__ __forceinline__ float stage_cost_culled(const InstDesc& d, float own_d2,
-                                                   float vref0, const LaneCull& lc,
-                                                   bool vref_uniform, bool act,
-                                                   int& seed, float x, float y,
-                                                   float c, float sn, float v, float Ua, float Ud,
-                                                   float ea, float ed, int t, int t_lo, int t_hi,
-                                                   float th, float xp, float yp)
-{
-    const float ds = fmaf(d.d_safe_c, v, d.d_safe_0);
-    const bool inc = act && isfinite(x) && isfinite(y);
-    const WaveBox wb = wave_box(inc, x, y, ds == ds ? ds : -INFINITY);
-    float ext;
-    float cost = path_cost_culled(d, wb, inc ? own_d2 : 0.0f, vref0, lc.box, vref_uniform, seed, x,
-                                  y, v, input_cost(d, Ua, Ud, ea, ed), th, xp, yp, ext);
-    if (NE > 0) {
-        const float d_obj =
-            obstacle_gap_culled<NE>(d, wb, lc.cpv, lc.crr, x, y, c, sn, t, t_lo, t_hi);
-        cost = fmaf(d.w_coll, safe_cost(d, ds, d_obj), cost);
-    }
-    return cost + ext;
 }
 
 // A float64 value of another lane by DPP (two 32-bit moves).
