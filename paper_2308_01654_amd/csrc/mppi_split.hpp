@@ -428,7 +428,8 @@ __device__ __forceinline__ void split_tile(const InstDesc& d, int tile, unsigned
 
 // One instance: a workgroup per tile.
 template <int G, int NE, bool M5, bool PS>
-__global__ __launch_bounds__(split_threads(NE)) void k_split(InstDesc d0)
+__global__ __launch_bounds__(split_threads(NE)) __attribute__((amdgpu_waves_per_eu(split_waves(G))))
+void k_split(InstDesc d0)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     split_tile<G, NE, M5, PS>(d0, blockIdx.x, smem);
@@ -436,7 +437,8 @@ __global__ __launch_bounds__(split_threads(NE)) void k_split(InstDesc d0)
 
 // The instances of class cls of a batch.
 template <int G, int NE, bool M5, bool PS>
-__global__ __launch_bounds__(split_threads(NE)) void k_split_batch(const BatchHdr* __restrict__ hdr, int cls)
+__global__ __launch_bounds__(split_threads(NE)) __attribute__((amdgpu_waves_per_eu(split_waves(G))))
+void k_split_batch(const BatchHdr* __restrict__ hdr, int cls)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     with_batch_tile(hdr, cls, blockIdx.x, [&](const InstDesc& d, int tile) {
