@@ -261,6 +261,12 @@ mppi_status mppi_set_staging(mppi_t* h, int32_t mode);
  * identical bit for bit.  MPPI_E_INVALID for other values. */
 mppi_status mppi_set_occupancy(mppi_t* h, int32_t mode);
 
+/* The iteration kernel of the handle's last step: 0 or 1 as for
+ * mppi_set_occupancy, 2 the kernel that gives the parts of a rollout to
+ * different waves (its results are those of the others bit for bit).
+ * MPPI_E_NOT_READY before the first step. */
+mppi_status mppi_get_kernel(mppi_t* h, int32_t* kernel);
+
 /* Wave-level culling of the two scans of the stage cost (on by default):
  * waypoint chunks and obstacle circles that provably cannot change any
  * lane's tracking minimum or obstacle cost are skipped.  Results are

@@ -1129,6 +1129,7 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
             hs[order[j]]->mail_behind = ws->behind;
         }
         hs[order[j]]->last_lanes = descs[j].lanes;
+        hs[order[j]]->last_occ = descs[j].occ;
         memcpy(hs[order[j]]->last_x0, x0s + 4 * order[j], sizeof(double) * 4);
         hs[order[j]]->last_steer0 = hs[order[j]]->steer0;
     }
@@ -1229,6 +1230,7 @@ mppi_status mppi_step_resident(mppi_t* h, const double x0[4])
                            h->stream));
     if ((s = record_end(h, 0, a)) != MPPI_OK) return s;
     h->last_lanes = d.lanes;
+    h->last_occ = d.occ;
     h->stepped = true;
     memcpy(h->last_x0, x0, sizeof(double) * 4);
     h->last_steer0 = h->steer0;
@@ -1481,6 +1483,16 @@ mppi_status mppi_set_occupancy(mppi_t* h, int32_t mode)
     if (mode < -1 || mode > kOccHigh)
         return fail(MPPI_E_INVALID, "occupancy mode must be -1, 0 or 1");
     h->occ_req = mode;
+    return MPPI_OK;
+}
+
+mppi_status mppi_get_kernel(mppi_t* h, int32_t* kernel)
+{
+    mppi_status s = usable(h);
+    if (s != MPPI_OK) return s;
+    if (!kernel) return fail(MPPI_E_INVALID, "kernel is NULL");
+    if (h->last_occ < 0) return fail(MPPI_E_NOT_READY, "no step has been taken");
+    *kernel = h->last_occ;
     return MPPI_OK;
 }
 

@@ -621,13 +621,13 @@ __device__ __forceinline__ float input_cost(const InstDesc& d, float Ua, float U
 // their own cost is not finite under either scan.  A safety distance beyond
 // float32 counts as +inf, near which every circle is; one that is not a number
 // costs nothing under either scan.  The scene is read from global memory
-// (wave-uniform candidates through the scalar
-// cache); own_d2 is the lane's squared distance to the nearest of three
-// waypoints ahead of its previous closest chunk (+inf without one), formed
-// by the caller, and vref0 the reference speed of waypoint 0.  One function: as
-// two, one for each scan, more of what both keep in scalar registers was spilled
-// (lane reads in the 16-lane kernel 774 against 456; 8192 x 100, 60 circles 37.0
-// -> 34.8 us, 16384 x 600, 12 circles 369 -> 337).
+// (wave-uniform candidates through the scalar cache); own_d2 is the lane's
+// squared distance to the nearest of three waypoints ahead of its previous
+// closest chunk (+inf without one), formed by the caller, and vref0 the
+// reference speed of waypoint 0.  One function: as two, one for each scan, more
+// of what both keep in scalar registers was spilled (lane reads in the 16-lane
+// kernel 774 against 459; 8192 x 100, 60 circles 37.0 -> 34.8 us, 16384 x 600, 12
+// circles 369 -> 337).
 template <int NE>
 __device__ __forceinline__ float stage_cost_culled(const InstDesc& d, float own_d2,
                                                    float vref0, const LaneCull& lc,

@@ -78,6 +78,7 @@ struct mppi {
     int occ_req = -1;   // -1 = tuning table, else kOccDefault or kOccHigh
     int no_cull = 0;    // 1: full waypoint and circle scans
     int last_lanes = 0;
+    int last_occ = -1;  // iteration kernel of the last step (kOcc...), -1: none yet
     mppi_status sticky = MPPI_OK;
     // device memory
     double* U = nullptr;

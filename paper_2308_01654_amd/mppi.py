@@ -138,6 +138,7 @@ SIGNATURES = [
     ("mppi_set_lanes_per_sample", _i32, [_vp, _i32]),
     ("mppi_set_staging", _i32, [_vp, _i32]),
     ("mppi_set_occupancy", _i32, [_vp, _i32]),
+    ("mppi_get_kernel", _i32, [_vp, ctypes.POINTER(_i32)]),
     ("mppi_set_culling", _i32, [_vp, _i32]),
     ("mppi_get_stream", _i32, [_vp, ctypes.POINTER(_vp)]),
     ("mppi_set_profiling", _i32, [_vp, _i32]),
@@ -363,6 +364,13 @@ class Planner:
     def set_occupancy(self, mode):
         """-1: tuning table, 0: default kernel, 1: the five-waves-per-SIMD kernel."""
         check(load().mppi_set_occupancy(self.h, int(mode)))
+
+    def kernel(self):
+        """The last step's iteration kernel: 0 or 1 as for set_occupancy, 2 the
+        one that gives the parts of a rollout to different waves."""
+        k = _i32()
+        check(load().mppi_get_kernel(self.h, ctypes.byref(k)))
+        return k.value
 
     def step(self, x0, waypoints, circles):
         scene, keep = make_scene(waypoints, circles)
