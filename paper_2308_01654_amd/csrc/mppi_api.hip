@@ -404,29 +404,53 @@ int auto_occ(const mppi_config& c, int n_c)
     return e ? e->occ : 0;
 }
 
-// Where the split kernel beats k_batch (K, T, circles: k_batch -> split, us):
-// at 16 lanes per sample everywhere measured (1024, 50, 3: 18.1 -> 12.3; 8192,
-// 100, 60: 36.8 -> 24.8; 2560, 16, 3: 12.4 -> 9.5); at 8 as well, by less
-// (16384, 24, 16: 17.3 -> 15.4; 24000, 64, 16: 42.0 -> 35.1; 65536, 100, 48: 158 ->
-// 127; 32768, 50, 60: 44.7 -> 45.3).  At 4 it needs a horizon long enough for
-// the samples to drift apart, and circles (65536, 64, 48: 99 -> 87; 131072, 64,
-// 16: 169 -> 156; but 65536, 40, 16: 52 -> 59 and 131072, 64, 0: 141 -> 146); at
-// 2 a span of 16 steps of a tile leaves no room for a second one, and it takes
-// 1.3 to 2 times as long.
-static bool split_pays(const mppi_config& c, int n_c, int lanes)
+// Where the split kernel beats k_batch.  It hides the latency of a chain behind
+// other waves, and it culls by rows, which pays once the samples have drifted
+// apart; it needs more waves for a sample, and its waves wait for one another.  So
+// it wins wherever the launch has at most two tiles for each of the 256 compute
+// units (us, k_batch -> split: 16 lanes, 1024 x 50, 3 circles 18.1 -> 12.3; 8192 x
+// 100, 60 circles 34.8 -> 23.2; 8 lanes, 16384 x 24, 12 circles 17.0 -> 15.3; 4
+// lanes, 32768 x 64, 60 circles 46 -> 35; a batch of 4 of 2048 x 16, 16 lanes: 1.06
+// times), and in larger launches from a horizon on:
+//  * 16 lanes, alone: always (16384 x 33: 1.1 to 1.2 times, 32768 x 150 1.2 to 1.6).
+//    In a batch (the descriptors come from memory) from 48 steps (2048 tiles: 32
+//    steps 0.96 to 0.99 times, 48 steps 1.03 to 1.08, 100 steps 1.06 to 1.16), with
+//    per-step weights from 64 (24 steps 0.90, 48 steps 0.97 to 0.99, 100 steps 1.17
+//    to 1.3); without circles always;
+//  * 8 lanes, alone: from 32 steps with circles that are all listed or none (1024
+//    tiles: 24 steps 0.93 to 0.97, 32 steps 1.05 to 1.07, 64 steps 1.05 to 1.18), else
+//    from 80 (200 and 512 circles: 50 steps 0.85 to 0.9, 64 steps 0.94 to 1.04, 80 steps
+//    1.0 to 1.13).  In a batch from 128 steps (2048 tiles: 80 steps 0.94 to 1.09, 128
+//    steps 1.1 to 1.35), with listed circles from 100 (1.02 to 1.14);
+//  * 4 lanes, alone: with listed circles while its tiles keep their perturbations
+//    (131072 x 64: 1.05 to 1.07; x 80 0.92 to 0.94), else from 128 steps (1.03 to 1.3).
+//    In a batch from 150 (2048 tiles: 128 steps 0.96 to 1.17, 150 steps 1.04 to 1.3).
+// Below 64 steps at 4 lanes, without circles there, with per-step weights below 16
+// lanes and at 2 lanes it is not used (131072 x 32 at 2: 86 -> 112).
+static bool split_pays(const mppi_config& c, int n_c, int lanes, bool staged, int tiles, bool alone)
 {
-    if (lanes == 16) return true;
-    if (c.per_step_weights) return false;
-    return lanes == 8 || (lanes == 4 && c.T >= 64 && n_c > 0);
+    if (lanes < 4 || (lanes < 16 && c.per_step_weights)) return false;
+    if (lanes == 4 && (c.T < 64 || n_c == 0)) return false;
+    if (tiles <= 2 * 256) return true;
+    const bool listed = n_c <= kListedCircles;
+    switch (lanes) {
+    case 16: return alone || n_c == 0 || c.T >= (c.per_step_weights ? 64 : 48);
+    case 8: return c.T >= (alone ? (listed ? 32 : 80) : (listed && n_c > 0 ? 100 : 128));
+    default: return c.T >= (alone ? 128 : 150) || (alone && listed && staged);
+    }
 }
 
-int occ_choice(const mppi_t* h, int n_wp, int n_c, int lanes, bool alone)
+int occ_choice(const mppi_t* h, int n_wp, int n_c, int lanes, int batch_tiles)
 {
     const mppi_config& c = h->cfg;
-    if (!h->no_cull && h->occ_req < 0 && split_pays(c, n_c, lanes)) {
-        const size_t lds = split_layout(c.T, n_wp, lanes, c.per_step_weights).total;
-        const bool one_each = alone && (long)c.K * lanes <= 256 * 256;  // at most a tile per compute unit
-        if (lds <= kSplitLds || (one_each && lds <= kSplitLdsAlone)) return kOccSplit;
+    const bool alone = batch_tiles == 0;
+    const int tiles = alone ? (int)(((long)c.K * lanes + kBlock - 1) / kBlock) : batch_tiles;
+    if (!h->no_cull && h->occ_req < 0 && lanes >= 4) {
+        const SplitLayout L = split_layout(c.T, n_wp, lanes, c.per_step_weights);
+        const bool one_each = alone && tiles <= 256;  // at most a tile per compute unit
+        if ((L.total <= kSplitLds || (one_each && L.total <= kSplitLdsAlone)) &&
+            split_pays(c, n_c, lanes, L.staged, tiles, alone))
+            return kOccSplit;
     }
     // the other compilations exist for 8 and 16 lanes per sample
     if (lanes < 8) return kOccDefault;
@@ -758,8 +782,6 @@ mppi_status handle_create(const mppi_config* cfg, void* hip_stream, bool with_sc
     return MPPI_OK;
 }
 
-// Descriptor of one iteration of handle h from state x0 on the scene at
-// `scene` (device), staged relative to `origin`.
 // Whether the tiles of d keep their perturbations in LDS (see kLdsShared).
 int stage_allowed(const mppi_t* h, int n_c)
 {
@@ -773,9 +795,11 @@ void choose_eps_stage(InstDesc& d, bool alone, int allowed)
                   (L.total <= kLdsShared || (alone && d.n_tiles <= 512 && L.total <= kLdsAlone));
 }
 
+// Descriptor of one iteration of handle h from state x0 on the scene at
+// `scene` (device), staged relative to `origin`; batch_tiles as for occ_choice.
 void fill_desc(InstDesc& d, const mppi_t* h, const double x0[4], const double origin[2],
                const unsigned char* scene, const SceneLayout& L, int n_wp, int n_c, int shift,
-               bool alone)
+               int batch_tiles)
 {
     const mppi_config& c = h->cfg;
     memset(&d, 0, sizeof d);
@@ -788,7 +812,7 @@ void fill_desc(InstDesc& d, const mppi_t* h, const double x0[4], const double or
     // two or more waves per SIMD (256 compute units x 4): the block-ordered
     // wave priority pays; with fewer it only costs its instructions
     d.wave_prio = (long)c.K * d.lanes >= 2L * 1024 * 64 ? 1 : 0;
-    d.occ = occ_choice(h, n_wp, n_c, d.lanes, alone);
+    d.occ = occ_choice(h, n_wp, n_c, d.lanes, batch_tiles);
     d.dt = (float)c.dt;
     d.inv_dt = (float)(1.0 / c.dt);
     d.inv_L = (float)(1.0 / c.wheelbase);
@@ -845,7 +869,7 @@ void fill_desc(InstDesc& d, const mppi_t* h, const double x0[4], const double or
     d.q = h->q;
     d.Stk = h->Stk;
     d.st = h->st;
-    choose_eps_stage(d, alone, stage_allowed(h, n_c));
+    choose_eps_stage(d, batch_tiles == 0, stage_allowed(h, n_c));
 }
 
 // ---- batched launches ---------------------------------------------------------------
@@ -950,14 +974,22 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
     // group by kernel variant, longest tiles first inside a group
     std::vector<int> order(n), cls(n);
     std::vector<double> work(n);
+    long total = 0;  // tiles of the batch
+    for (int i = 0; i < n; ++i) {
+        const int nc = scenes ? scenes[i].n_circles : hs[i]->n_c;
+        cls[i] = hs[i]->lanes_req ? hs[i]->lanes_req : auto_lanes(hs[i]->cfg, nc);
+        total += ((long)hs[i]->cfg.K * cls[i] + kBlock - 1) / kBlock;
+    }
+    if (total > (1L << 30)) return fail(MPPI_E_INVALID, "batch too large");
+    const int batch_tiles = (int)total;
     for (int i = 0; i < n; ++i) {
         const mppi_config& c = hs[i]->cfg;
         const int nw = scenes ? scenes[i].n_waypoints : hs[i]->n_wp;
         const int nc = scenes ? scenes[i].n_circles : hs[i]->n_c;
-        const int g = hs[i]->lanes_req ? hs[i]->lanes_req : auto_lanes(c, nc);
+        const int g = cls[i];
         const int gi = g == 1 ? 0 : g == 2 ? 1 : g == 4 ? 2 : g == 8 ? 3 : 4;
         order[i] = i;
-        const int occ = occ_choice(hs[i], nw, nc, g, false);
+        const int occ = occ_choice(hs[i], nw, nc, g, batch_tiles);
         cls[i] = 50 * occ + 25 * (c.model ? 1 : 0) +
                  5 * (occ == kOccSplit && c.per_step_weights ? 0 : gi) + active_ego(c.n_ego, nc);
         work[i] = (double)c.T * (73.0 + 6.0 * nw + 7.0 * c.n_ego * nc);
@@ -984,7 +1016,7 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
     BatchHdr* hdr = reinterpret_cast<BatchHdr*>(host);
     int* prefix = reinterpret_cast<int*>(host + off_prefix);
     InstDesc* descs = reinterpret_cast<InstDesc*>(host + off_descs);
-    long total = 0;
+    total = 0;
     size_t smem = 0, smem_split = 0;
     int any_shift = 0, any_out = 0, combine_g = 0, max_nodes = 0, most_tiles = 0;
     for (int j = 0; j < n; ++j) {
@@ -997,10 +1029,10 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
             const double origin[2] = {x0[0], x0[1]};
             write_scene(host + soff[i], lay[i], hi->cfg, origin, &scenes[i]);
             fill_desc(descs[j], hi, x0, origin, ws->arena + soff[i], lay[i], scenes[i].n_waypoints,
-                      scenes[i].n_circles, sh, false);
+                      scenes[i].n_circles, sh, batch_tiles);
         } else {
             fill_desc(descs[j], hi, x0, hi->origin, hi->scene, hi->lay, hi->n_wp, hi->n_c, sh,
-                      false);
+                      batch_tiles);
         }
         if (ex) {
             descs[j].S = ex->S;
@@ -1024,7 +1056,6 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
         max_nodes = std::max(max_nodes, combine_nodes(descs[j].n_tiles, nullptr));
         if (!descs[j].per_step) most_tiles = std::max(most_tiles, descs[j].n_tiles);
     }
-    if (total > (1L << 30)) return fail(MPPI_E_INVALID, "batch too large");
     prefix[n] = (int)total;
     hdr->n_inst = n;
     hdr->total_tiles = (int)total;
@@ -1217,7 +1248,7 @@ mppi_status mppi_step_resident(mppi_t* h, const double x0[4])
         if (!isfinite(x0[i])) return fail(MPPI_E_INVALID, "x0[%d] is not finite", i);
     changes_results(h);
     InstDesc d;
-    fill_desc(d, h, x0, h->origin, h->scene, h->lay, h->n_wp, h->n_c, 0, true);
+    fill_desc(d, h, x0, h->origin, h->scene, h->lay, h->n_wp, h->n_c, 0, 0);
     hipEvent_t a = nullptr;
     if ((s = record_launch(h, 0, &a)) != MPPI_OK) return s;
     hipEvent_t a2 = nullptr;

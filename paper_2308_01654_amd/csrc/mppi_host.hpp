@@ -163,7 +163,7 @@ mppi_status record_launch(mppi_t* h, int kind, hipEvent_t* a);
 mppi_status record_end(mppi_t* h, int kind, hipEvent_t a);
 void fill_desc(InstDesc& d, const mppi_t* h, const double x0[4], const double origin[2],
                const unsigned char* scene, const SceneLayout& L, int n_wp, int n_c, int shift,
-               bool alone);
+               int batch_tiles);
 // Whether the tiles of d keep their perturbations in LDS: within kLdsShared,
 // or within kLdsAlone for an instance launched alone (alone = true) with at
 // most 512 tiles.
@@ -177,7 +177,9 @@ int auto_stage(const mppi_config& c, int n_c);
 // applies, else the tuning table's choice (kOccDefault when it has no such
 // column; kOccDefault below 8 lanes per sample).
 int auto_occ(const mppi_config& c, int n_c);
-int occ_choice(const mppi_t* h, int n_wp, int n_c, int lanes, bool alone);
+// batch_tiles: the tiles of the batch it is launched in, 0 for an instance
+// launched alone.
+int occ_choice(const mppi_t* h, int n_wp, int n_c, int lanes, int batch_tiles);
 mppi_status ws_create(BatchWs** out);
 void ws_destroy(BatchWs* b);
 // Create a handle; with_scratch = false leaves S/eps/partials/scales/scene

@@ -60,3 +60,48 @@ def test_grouped_circles_run_the_split_kernel(n_c):
     """Scenes of test_grouped_circles_bit_identical, with culling and without."""
     assert _kernels(200, 60, n_c, 221, {}, 16) == [SPLIT, 0]
     assert _kernels(200, 60, n_c, 221, {}, 16, cull=False) == [0, 0]
+
+
+# On either side of each line of the rule: 512 tiles (two per compute unit) and
+# more, alone and in a batch of n; horizons; circles that are all listed (up to
+# 64), more, none; per-step weights.  At 4 lanes and 90 steps the tiles do not keep
+# their perturbations.
+@pytest.mark.parametrize("lanes,n,K,T,n_c,ps,split", [
+    (16, 1, 8208, 16, 12, 0, 1), (16, 2, 4096, 16, 12, 0, 1), (16, 3, 2736, 47, 12, 0, 0),
+    (16, 3, 2736, 48, 12, 0, 1), (16, 3, 2736, 16, 0, 0, 1), (16, 3, 2736, 63, 65, 1, 0),
+    (16, 3, 2736, 64, 65, 1, 1), (16, 2, 4096, 16, 12, 1, 1),
+    (8, 1, 16384, 24, 12, 0, 1), (8, 1, 16384, 24, 12, 1, 0), (8, 1, 16416, 31, 12, 0, 0),
+    (8, 1, 16416, 32, 64, 0, 1), (8, 1, 16416, 32, 0, 0, 1), (8, 1, 16416, 79, 65, 0, 0),
+    (8, 1, 16416, 80, 65, 0, 1), (8, 2, 8192, 24, 12, 0, 1), (8, 2, 8224, 99, 12, 0, 0),
+    (8, 2, 8224, 100, 12, 0, 1), (8, 2, 8224, 100, 0, 0, 0), (8, 2, 8224, 127, 65, 0, 0),
+    (8, 2, 8224, 128, 65, 0, 1),
+    (4, 1, 32768, 63, 12, 0, 0), (4, 1, 32768, 64, 12, 0, 1), (4, 1, 32768, 64, 0, 0, 0),
+    (4, 1, 32832, 64, 12, 0, 1), (4, 1, 32832, 64, 65, 0, 0), (4, 1, 32832, 90, 12, 0, 0),
+    (4, 1, 32832, 128, 65, 0, 1), (4, 2, 16448, 149, 12, 0, 0), (4, 2, 16448, 150, 12, 0, 1),
+    (2, 1, 2048, 100, 12, 0, 0),
+])
+def test_rule_of_the_split_kernel(lanes, n, K, T, n_c, ps, split):
+    """The kernel that is launched, with the bits of the other one."""
+    mppi = _mppi()
+    rng = np.random.Generator(np.random.PCG64(T))
+    sc = scenes.tiny(K=K, T=T, n_c=0, seed=3)
+    p = dict(sc["params"], per_step=ps)
+    ci = scenes.sine_circles(rng, n_c, 0.0, 60.0)
+    print("  case:", lanes, n, K, T, n_c, ps, flush=True)
+    lead = mppi.Planner(p, lanes=lanes)
+    pls = [lead] + [mppi.Planner(p, lanes=lanes, hip_stream=lead.stream()) for _ in range(n - 1)]
+    try:
+        if n == 1:
+            lead.step(sc["x0"], sc["waypoints"], ci)
+        else:
+            mppi.step_batch(pls, np.array([sc["x0"]] * n), [(sc["waypoints"], ci)] * n)
+        assert [pl.kernel() == SPLIT for pl in pls] == [bool(split)] * n
+        with mppi.Planner(p, lanes=lanes) as ref:
+            ref.set_occupancy(0)
+            ref.step(sc["x0"], sc["waypoints"], ci)
+            assert ref.kernel() == 0
+            assert np.array_equal(pls[-1].costs(), ref.costs())
+            assert np.array_equal(pls[-1].controls(), ref.controls())
+    finally:
+        for pl in reversed(pls):
+            pl.close()
