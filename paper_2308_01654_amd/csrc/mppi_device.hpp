@@ -4,7 +4,6 @@
 // stage cost and its culling, and wave reductions.
 #pragma once
 
-#include <float.h>
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -659,16 +658,15 @@ __device__ __forceinline__ float stage_cost_culled(const InstDesc& d, float own_
     };
     // A second bound from the lane itself: its distance^2 to three waypoints
     // ahead of the chunk it was closest to at its previous step (seed), the
-    // largest over the lanes of the wave; lanes without a seed give +inf.  The
-    // threshold stays finite where every squared distance is beyond float32, so
-    // that it is never met by the empty boxes past the last chunk (at +inf).
-    auto limit = [](float ub) { return fminf(fmaf(ub, 1.0f + 1e-5f, 1e-6f), FLT_MAX); };
+    // largest over the lanes of the wave; lanes without a seed give +inf.  (A
+    // chunk must lie below the threshold: one at +inf, like the empty boxes past
+    // the last chunk, is never a candidate, even where the threshold is +inf.)
     const float own = inc ? own_d2 : 0.0f;
     if (n_ch <= 64) {
         float ub_box, ub_own;
         wave_minmax_nonneg(far2(lc.box), own, ub_box, ub_own);
-        const float thr = limit(fminf(ub_box, ub_own));
-        scan_chunks(wp4, 0, __ballot(near2(lc.box) <= thr), x, y, best, bch);
+        const float thr = fmaf(fminf(ub_box, ub_own), 1.0f + 1e-5f, 1e-6f);
+        scan_chunks(wp4, 0, __ballot(near2(lc.box) < thr), x, y, best, bch);
     } else {
         const float4 empty = make_float4(INFINITY, -INFINITY, INFINITY, -INFINITY);
         float ub, ub_own;
@@ -676,11 +674,11 @@ __device__ __forceinline__ float stage_cost_culled(const InstDesc& d, float own_
         ub = fminf(ub, ub_own);
         for (int base = 64; base < n_ch; base += 64)
             ub = fminf(ub, wave_min_nonneg(far2(base + lane < n_ch ? ld_g(d.wp_box, base + lane) : empty)));
-        const float thr = limit(ub);
-        scan_chunks(wp4, 0, __ballot(near2(lc.box) <= thr), x, y, best, bch);
+        const float thr = fmaf(ub, 1.0f + 1e-5f, 1e-6f);
+        scan_chunks(wp4, 0, __ballot(near2(lc.box) < thr), x, y, best, bch);
         for (int base = 64; base < n_ch; base += 64) {
             const float4 b = base + lane < n_ch ? ld_g(d.wp_box, base + lane) : empty;
-            scan_chunks(wp4, base, __ballot(near2(b) <= thr), x, y, best, bch);
+            scan_chunks(wp4, base, __ballot(near2(b) < thr), x, y, best, bch);
         }
     }
     if (best < INFINITY) seed = bch;
@@ -773,12 +771,13 @@ __device__ __forceinline__ unsigned row_bits(unsigned long long b)
 
 // Row reductions of five values, two to their minima and three to their
 // maxima, in every lane of the row.  Written out with the float minimum and
-// maximum, which pass over a value that is not a number (the ego centres of a
-// heading beyond float32): the compiler would quiet every moved value first, and
-// the integer keys of the reductions above cost their way there and back (with the waves without columns leaving early: 6093 -> 5640
-// vector instructions per four samples of the sine lane, 26.5 -> 24.8 us an
-// iteration).  Four instructions lie between an instruction and the next
-// that moves its result, as a lane move needs two.
+// maximum, which pass over a value that is not a number (a safety distance, the
+// ego centres of a heading beyond float32): the compiler would quiet every moved
+// value first, and the integer keys of the reductions above cost their way there
+// and back (with the waves without columns leaving early: 6093 -> 5640 vector
+// instructions per four samples of the sine lane, 26.5 -> 24.8 us an iteration).
+// Four instructions lie between an instruction and the next that moves its
+// result, as a lane move needs two.
 __device__ __forceinline__ void row_reduce5(float& a, float& b, float& c, float& e, float& f)
 {
 #define MPPI_STAGE(CTRL)                                              \
@@ -824,10 +823,12 @@ __device__ __forceinline__ float path_cost_rows(const InstDesc& d, const float4*
     float xhi = inc ? x : -INFINITY, yhi = inc ? y : -INFINITY;
     row_reduce5(xlo, ylo, xhi, yhi, own);
     const float thr = fmaf(own, 1.0f + 1e-5f, 1e-6f);
-    auto near = [&](const float4& bx) {  // smallest distance^2, row box to chunk box
+    // smallest distance^2, row box to chunk box, below the threshold (never the
+    // empty boxes past the last chunk, at +inf)
+    auto near = [&](const float4& bx) {
         const float gx = fmaxf(fmaxf(bx.x - xhi, xlo - bx.y), 0.0f);
         const float gy = fmaxf(fmaxf(bx.z - yhi, ylo - bx.w), 0.0f);
-        return fmaf(gy, gy, gx * gx) <= thr;
+        return fmaf(gy, gy, gx * gx) < thr;
     };
     // first and last candidate chunk of the row (those between are scanned too)
     int lo = 0x7fffffff, hi = -1;
@@ -846,9 +847,6 @@ __device__ __forceinline__ float path_cost_rows(const InstDesc& d, const float4*
             take(i, ch < n_ch && near(ld_g(d.wp_box, min(ch, n_ch - 1))));
         }
     }
-    // (the empty boxes past the last chunk are near, too, where the bound is
-    // beyond float32)
-    hi = min(hi, n_ch - 1);
     lo = max(min(lo, hi), 0);
     float best = INFINITY;
     int bch = 0;
@@ -912,19 +910,19 @@ __device__ __forceinline__ void put_circle(float4* list, int e, const float4& p,
     list[2 * e + 1] = make_float4(rr, reach, 0.0f, 0.0f);
 }
 // A box of ego circle centres as centre and half extent (widened by the
-// rounding of forming them; -inf for a box without centres, which is near
-// nothing), and the largest distance from a centre at which an obstacle circle
-// counts.
+// rounding of forming them), and the largest distance from a centre at which an
+// obstacle circle counts.  A box without centres runs from kNowhere to -kNowhere:
+// its half extent is so far below zero that nothing is near it.
+constexpr float kNowhere = 1e30f;
 struct EgoBox {
     float xc, yc, xh, yh, ds;
 };
 __device__ __forceinline__ EgoBox ego_box(const InstDesc& d, const WaveBox& b)
 {
     EgoBox o;
-    const bool none = b.xlo > b.xhi;
-    o.xc = none ? 0.0f : 0.5f * (b.xlo + b.xhi);
+    o.xc = 0.5f * (b.xlo + b.xhi);
     o.yc = 0.5f * (b.ylo + b.yhi);
-    o.xh = none ? -INFINITY : fmaf(1e-6f, fabsf(b.xlo) + fabsf(b.xhi), 0.5f * (b.xhi - b.xlo));
+    o.xh = fmaf(1e-6f, fabsf(b.xlo) + fabsf(b.xhi), 0.5f * (b.xhi - b.xlo));
     o.yh = fmaf(1e-6f, fabsf(b.ylo) + fabsf(b.yhi), 0.5f * (b.yhi - b.ylo));
     o.ds = d.coll_only ? 0.0f : b.dsmax;
     return o;
@@ -1023,11 +1021,11 @@ __device__ __forceinline__ float obstacle_cost_rows(const InstDesc& d, float4* l
         yh = fmaxf(yh, ey[e]);
     }
     WaveBox row;
-    row.xlo = inc ? xl : INFINITY;
-    row.ylo = inc ? yl : INFINITY;
-    row.xhi = inc ? xh : -INFINITY;
-    row.yhi = inc ? yh : -INFINITY;
-    row.dsmax = inc && ds == ds ? ds : -INFINITY;
+    row.xlo = inc ? xl : kNowhere;
+    row.ylo = inc ? yl : kNowhere;
+    row.xhi = inc ? xh : -kNowhere;
+    row.yhi = inc ? yh : -kNowhere;
+    row.dsmax = inc ? ds : -kNowhere;
     row_reduce5(row.xlo, row.ylo, row.xhi, row.yhi, row.dsmax);
     const EgoBox rb = ego_box(d, row);
     // the middle of the span's times (of a span that starts before the horizon
@@ -1049,7 +1047,7 @@ __device__ __forceinline__ float obstacle_cost_rows(const InstDesc& d, float4* l
         return safe_cost(d, ds, d_obj);
     }
     const WaveBox wbox = wave_box_of_rows({fkey(row.xlo), fkey(row.ylo), fkey(row.xhi), fkey(row.yhi),
-                                           fkey(row.dsmax)});
+                                           fkey(fmaxf(row.dsmax, -kNowhere))});  // (a number)
     const EgoBox wb = ego_box(d, wbox);
     int cnt = 0;
     auto flush = [&]() {
@@ -1059,10 +1057,9 @@ __device__ __forceinline__ float obstacle_cost_rows(const InstDesc& d, float4* l
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
                 const int e = j + 16 * u + r;
-                const float4* q = list + 2 * (e < cnt ? 1 + e : 0);
+                const float4* q = list + 2 * (1 + e);  // (past the last entry: within the list)
                 const float4 p = q[0];
-                const bool n = e < cnt &&
-                               circle_near(rb, fmaf(tau_m, p.z, p.x), fmaf(tau_m, p.w, p.y), q[1].y);
+                const bool n = circle_near(rb, fmaf(tau_m, p.z, p.x), fmaf(tau_m, p.w, p.y), q[1].y) && e < cnt;
                 m |= row_bits(__ballot(n)) << (16 * u);
             }
             d_obj = row_circle_scan<NE>(list, 1 + j, m, ex, ey, tau, d_obj);

@@ -288,7 +288,7 @@ inline __host__ __device__ constexpr int split_threads(int ne) { return kBlock *
 // one workgroup of these fitted a compute unit (131072 x 64, 512 circles, 4 ego
 // circles 720 us against 439 with six; a batch of four of 65536 x 100, 12 circles,
 // 3 ego circles 660 against 460).  (At 16 it takes at most 73 by itself.)
-inline constexpr int split_waves(int lanes) { return lanes < 16 ? 6 : 3; }
+inline constexpr int split_waves(int lanes, int ne) { return lanes < 16 ? 6 : split_threads(ne) / 256; }
 // Two workgroups of the split kernel share a compute unit's 160 KB of LDS.
 // With more it is one, and k_batch's four are the faster again once every
 // unit has a tile.

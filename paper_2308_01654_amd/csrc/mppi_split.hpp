@@ -428,7 +428,7 @@ __device__ __forceinline__ void split_tile(const InstDesc& d, int tile, unsigned
 
 // One instance: a workgroup per tile.
 template <int G, int NE, bool M5, bool PS>
-__global__ __launch_bounds__(split_threads(NE)) __attribute__((amdgpu_waves_per_eu(split_waves(G))))
+__global__ __launch_bounds__(split_threads(NE)) __attribute__((amdgpu_waves_per_eu(split_waves(G, NE))))
 void k_split(InstDesc d0)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -437,7 +437,7 @@ void k_split(InstDesc d0)
 
 // The instances of class cls of a batch.
 template <int G, int NE, bool M5, bool PS>
-__global__ __launch_bounds__(split_threads(NE)) __attribute__((amdgpu_waves_per_eu(split_waves(G))))
+__global__ __launch_bounds__(split_threads(NE)) __attribute__((amdgpu_waves_per_eu(split_waves(G, NE))))
 void k_split_batch(const BatchHdr* __restrict__ hdr, int cls)
 {
     extern __shared__ __align__(16) unsigned char smem[];
