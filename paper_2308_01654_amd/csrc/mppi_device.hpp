@@ -292,6 +292,7 @@ __device__ __forceinline__ float fkey_inv(int k)
 {
     return __builtin_bit_cast(float, k ^ ((k >> 31) & 0x7fffffff));
 }
+constexpr float kNowhere = 1e30f;               // where nothing is: positions, distances below zero
 constexpr int kKeyPosInf = 0x7f800000;          // fkey(+inf)
 constexpr int kKeyNegInf = (int)0x807fffffu;    // fkey(-inf)
 
@@ -639,7 +640,7 @@ __device__ __forceinline__ float stage_cost_culled(const InstDesc& d, float own_
     const int lane = threadIdx.x & 63;
     const float ds = fmaf(d.d_safe_c, v, d.d_safe_0);
     const bool inc = act && isfinite(x) && isfinite(y) && isfinite(v);
-    const WaveBox wb = wave_box(inc, x, y, ds == ds ? ds : -INFINITY);
+    const WaveBox wb = wave_box(inc, x, y, fmaxf(ds, -kNowhere));
 
     // ---- waypoints
     const int n_ch = (d.n_wp + kChunk - 1) / kChunk;
@@ -913,7 +914,6 @@ __device__ __forceinline__ void put_circle(float4* list, int e, const float4& p,
 // rounding of forming them), and the largest distance from a centre at which an
 // obstacle circle counts.  A box without centres runs from kNowhere to -kNowhere:
 // its half extent is so far below zero that nothing is near it.
-constexpr float kNowhere = 1e30f;
 struct EgoBox {
     float xc, yc, xh, yh, ds;
 };
