@@ -631,8 +631,29 @@ static void changes_results(mppi_t* h)
     h->captured = true;
 }
 
-// U's first nu values and the device state into the handle's pinned buffer,
-// unless the batch that set them leaves them there.
+// Whether the batch that set U and the device state leaves them in the handle's
+// pinned buffer, with no work of its handles enqueued since.
+static bool mailed(const mppi_t* h)
+{
+    return h->mail && !h->mail_behind->load(std::memory_order_relaxed);
+}
+
+// U's first nu values and the device state into that buffer, by one small kernel
+// that then sets the handle's word to h->seq.
+static mppi_status enqueue_export(mppi_t* h, int nu)
+{
+    const mppi_status s = host_buffers(h);
+    if (s != MPPI_OK) return s;
+    mail_behind(h);
+    ++h->seq;
+    HIP_TRY(launch_export_controls(h->U, nu, h->st, h->ctl_dev,
+                                   reinterpret_cast<DevState*>(h->ctl_dev + 2 * h->cfg.T), h->done_dev,
+                                   h->seq, h->stream));
+    return MPPI_OK;
+}
+
+// U's first nu values and the device state in the handle's pinned buffer, after
+// everything enqueued so far.
 static mppi_status export_results(mppi_t* h, int nu)
 {
     // What the caller has enqueued on the stream since the batch is waited for as
@@ -640,7 +661,7 @@ static mppi_status export_results(mppi_t* h, int nu)
     // kernel retires, so behind other work of the batch's handles, which they
     // know of, an export is the faster way (64 handles, controls and trajectory
     // of each in turn: 38.4 us a handle with the question, 25.9 this way).
-    if (h->mail && !h->mail_behind->load(std::memory_order_relaxed)) {
+    if (mailed(h)) {
         const mppi_status s = wait_done(h, h->done, h->mail);
         if (s != MPPI_OK) return s;
         if (hipStreamQuery(h->stream) != hipSuccess) {
@@ -649,14 +670,8 @@ static mppi_status export_results(mppi_t* h, int nu)
         }
         return MPPI_OK;
     }
-    mppi_status s = host_buffers(h);
-    if (s != MPPI_OK) return s;
-    mail_behind(h);
-    const uint32_t seq = ++h->seq;
-    HIP_TRY(launch_export_controls(h->U, nu, h->st, h->ctl_dev,
-                                   reinterpret_cast<DevState*>(h->ctl_dev + 2 * h->cfg.T), h->done_dev,
-                                   seq, h->stream));
-    return wait_done(h, h->done, seq);
+    const mppi_status s = enqueue_export(h, nu);
+    return s == MPPI_OK ? wait_done(h, h->done, h->seq) : s;
 }
 
 // The device state after everything enqueued so far: written by one small
@@ -675,11 +690,12 @@ static mppi_status sync_status(mppi_t* h)
         HIP_TRY(hipStreamSynchronize(h->stream));
         return MPPI_OK;
     }
-    DevState st;
-    const mppi_status s = read_state(h, &st);
+    // The stream is synchronised at once: waiting for the word first and for the
+    // stream after it takes 14.8 us where this takes 11.6.
+    const mppi_status s = mailed(h) ? MPPI_OK : enqueue_export(h, 0);
     if (s != MPPI_OK) return s;
     HIP_TRY(hipStreamSynchronize(h->stream));
-    if (st.status != 0)
+    if (reinterpret_cast<const DevState*>(h->ctl_host + 2 * h->cfg.T)->status != 0)
         return fail(MPPI_E_NONFINITE, "every sample cost of the last step was non-finite");
     return MPPI_OK;
 }
