@@ -417,25 +417,42 @@ int auto_occ(const mppi_config& c, int n_c)
 //    steps 0.96 to 0.99 times, 48 steps 1.03 to 1.08, 100 steps 1.06 to 1.16), with
 //    per-step weights from 64 (24 steps 0.90, 48 steps 0.97 to 0.99, 100 steps 1.17
 //    to 1.3); without circles always;
-//  * 8 lanes, alone: from 32 steps with circles that are all listed or none (1024
-//    tiles: 24 steps 0.93 to 0.97, 32 steps 1.05 to 1.07, 64 steps 1.05 to 1.18), else
-//    from 80 (200 and 512 circles: 50 steps 0.85 to 0.9, 64 steps 0.94 to 1.04, 80 steps
-//    1.0 to 1.13).  In a batch from 128 steps (2048 tiles: 80 steps 0.94 to 1.09, 128
-//    steps 1.1 to 1.35), with listed circles from 100 (1.02 to 1.14);
+//  * 8 lanes, alone: from 32 steps with circles that are all listed (1024 tiles: 24
+//    steps 0.93, 32 steps 1.05 to 1.07, 64 steps 1.15 to 1.18), else from 80 (200 and
+//    512 circles: 50 steps 0.85 to 0.9, 64 steps 0.94 to 1.04, 80 steps 1.0 to 1.13;
+//    none: 50 steps 0.9 to 1.06, 80 steps 1.04 to 1.1).  In a batch from 128 steps
+//    (2048 tiles: 80 steps 0.94 to 1.09, 128 steps 1.1 to 1.35), with listed circles
+//    from 100 (1.02 to 1.14);
 //  * 4 lanes, alone: with listed circles while its tiles keep their perturbations
 //    (131072 x 64: 1.05 to 1.07; x 80 0.92 to 0.94), else from 128 steps (1.03 to 1.3).
 //    In a batch from 150 (2048 tiles: 128 steps 0.96 to 1.17, 150 steps 1.04 to 1.3).
+// Paths of more than 64 chunks, whose boxes a wave then reads 16 at a time for
+// every row, take what the circles' groups do not win back.  In launches of few
+// tiles it pays up to 1536 waypoints at 16 lanes (8192 x 50: 1000 waypoints 1.01 to
+// 1.17 times, 2048 0.9 to 1.04; x 100: 1500 1.3), below them up to 640 (16384 x 50 at
+// 8: 520 waypoints 0.98 to 1.13, 1000 0.86 to 1.03), from 100 steps 1024 (1000: 0.96 to
+// 1.3), with grouped circles always (1.05 to 1.3).  In larger ones with grouped
+// circles up to 1024 (8 lanes, 65536 x 100: 1000 waypoints 1.01 to 1.13, 2048 0.9), from
+// 100 steps 1536 (with 512 circles 1500: 1.25), from 150 always (x 200, 2048: 1.3 to
+// 1.5); with listed ones from 200 steps up to 640 (1.06 to 1.3; 100 steps 0.8 to 1.1).
 // Below 64 steps at 4 lanes, without circles there, with per-step weights below 16
 // lanes and at 2 lanes it is not used (131072 x 32 at 2: 86 -> 112).
-static bool split_pays(const mppi_config& c, int n_c, int lanes, bool staged, int tiles, bool alone)
+static bool split_pays(const mppi_config& c, int n_wp, int n_c, int lanes, bool staged, int tiles, bool alone)
 {
     if (lanes < 4 || (lanes < 16 && c.per_step_weights)) return false;
     if (lanes == 4 && (c.T < 64 || n_c == 0)) return false;
-    if (tiles <= 2 * 256) return true;
-    const bool listed = n_c <= kListedCircles;
+    const bool few = tiles <= 2 * 256, listed = n_c <= kListedCircles;
+    if (n_wp > 64 * kChunk) {
+        const int most =
+            few ? (!listed ? kMaxWaypoints : lanes == 16 ? 1536 : c.T >= 100 ? 1024 : 640)
+                : (!listed ? (c.T >= 150 ? kMaxWaypoints : c.T >= 100 ? 1536 : 1024)
+                           : (n_c > 0 && c.T >= 200 ? 640 : 0));
+        if (n_wp > most) return false;
+    }
+    if (few) return true;
     switch (lanes) {
     case 16: return alone || n_c == 0 || c.T >= (c.per_step_weights ? 64 : 48);
-    case 8: return c.T >= (alone ? (listed ? 32 : 80) : (listed && n_c > 0 ? 100 : 128));
+    case 8: return c.T >= (alone ? (listed && n_c > 0 ? 32 : 80) : (listed && n_c > 0 ? 100 : 128));
     default: return c.T >= (alone ? 128 : 150) || (alone && listed && staged);
     }
 }
@@ -449,7 +466,7 @@ int occ_choice(const mppi_t* h, int n_wp, int n_c, int lanes, int batch_tiles)
         const SplitLayout L = split_layout(c.T, n_wp, lanes, c.per_step_weights);
         const bool one_each = alone && tiles <= 256;  // at most a tile per compute unit
         if ((L.total <= kSplitLds || (one_each && L.total <= kSplitLdsAlone)) &&
-            split_pays(c, n_c, lanes, L.staged, tiles, alone))
+            split_pays(c, n_wp, n_c, lanes, L.staged, tiles, alone))
             return kOccSplit;
     }
     // the other compilations exist for 8 and 16 lanes per sample

@@ -71,7 +71,8 @@ def test_grouped_circles_run_the_split_kernel(n_c):
     (16, 3, 2736, 48, 12, 0, 1), (16, 3, 2736, 16, 0, 0, 1), (16, 3, 2736, 63, 65, 1, 0),
     (16, 3, 2736, 64, 65, 1, 1), (16, 2, 4096, 16, 12, 1, 1),
     (8, 1, 16384, 24, 12, 0, 1), (8, 1, 16384, 24, 12, 1, 0), (8, 1, 16416, 31, 12, 0, 0),
-    (8, 1, 16416, 32, 64, 0, 1), (8, 1, 16416, 32, 0, 0, 1), (8, 1, 16416, 79, 65, 0, 0),
+    (8, 1, 16416, 32, 64, 0, 1), (8, 1, 16416, 79, 0, 0, 0), (8, 1, 16416, 80, 0, 0, 1),
+    (8, 1, 16416, 79, 65, 0, 0),
     (8, 1, 16416, 80, 65, 0, 1), (8, 2, 8192, 24, 12, 0, 1), (8, 2, 8224, 99, 12, 0, 0),
     (8, 2, 8224, 100, 12, 0, 1), (8, 2, 8224, 100, 0, 0, 0), (8, 2, 8224, 127, 65, 0, 0),
     (8, 2, 8224, 128, 65, 0, 1),
@@ -82,12 +83,31 @@ def test_grouped_circles_run_the_split_kernel(n_c):
 ])
 def test_rule_of_the_split_kernel(lanes, n, K, T, n_c, ps, split):
     """The kernel that is launched, with the bits of the other one."""
+    _check(lanes, n, K, T, n_c, ps, split, scenes.tiny()["waypoints"])
+
+
+# Paths around 64 chunks of 8 waypoints and the lines past them, in launches of few
+# tiles and of more, with circles that are listed and in groups
+@pytest.mark.parametrize("lanes,K,T,n_c,n_wp,split", [
+    (16, 300, 20, 12, 1536, 1), (16, 300, 20, 12, 1537, 0), (16, 300, 20, 65, 2048, 1),
+    (8, 300, 20, 12, 640, 1), (8, 300, 20, 0, 641, 0), (8, 300, 20, 65, 2048, 1),
+    (8, 300, 100, 12, 1024, 1), (8, 300, 100, 12, 1025, 0),
+    (16, 8208, 20, 12, 512, 1), (16, 8208, 20, 12, 513, 0), (16, 8208, 20, 65, 1024, 1),
+    (16, 8208, 20, 65, 1025, 0), (16, 8208, 100, 65, 1536, 1), (16, 8208, 100, 65, 1537, 0),
+    (16, 8208, 150, 65, 2048, 1), (16, 8208, 200, 12, 640, 1), (16, 8208, 200, 12, 641, 0),
+    (16, 8208, 199, 12, 640, 0), (8, 16416, 200, 0, 513, 0),
+])
+def test_rule_of_the_split_kernel_for_long_paths(lanes, K, T, n_c, n_wp, split):
+    _check(lanes, 1, K, T, n_c, 0, split, parity._bent(n_wp, 0.5))
+
+
+def _check(lanes, n, K, T, n_c, ps, split, waypoints):
     mppi = _mppi()
     rng = np.random.Generator(np.random.PCG64(T))
-    sc = scenes.tiny(K=K, T=T, n_c=0, seed=3)
+    sc = dict(scenes.tiny(K=K, T=T, n_c=0, seed=3), waypoints=waypoints)
     p = dict(sc["params"], per_step=ps)
     ci = scenes.sine_circles(rng, n_c, 0.0, 60.0)
-    print("  case:", lanes, n, K, T, n_c, ps, flush=True)
+    print("  case:", lanes, n, K, T, n_c, ps, len(waypoints), flush=True)
     lead = mppi.Planner(p, lanes=lanes)
     pls = [lead] + [mppi.Planner(p, lanes=lanes, hip_stream=lead.stream()) for _ in range(n - 1)]
     try:
