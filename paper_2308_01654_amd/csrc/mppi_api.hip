@@ -457,6 +457,13 @@ static bool split_pays(const mppi_config& c, int n_wp, int n_c, int lanes, bool 
     }
 }
 
+// The compilation of k_batch; the second exists for 8 and 16 lanes per sample.
+static int k_batch_occ(const mppi_t* h, int n_c, int lanes)
+{
+    if (lanes < 8) return kOccDefault;
+    return h->occ_req >= 0 ? h->occ_req : auto_occ(h->cfg, n_c);
+}
+
 int occ_choice(const mppi_t* h, int n_wp, int n_c, int lanes, int batch_tiles)
 {
     const mppi_config& c = h->cfg;
@@ -469,9 +476,15 @@ int occ_choice(const mppi_t* h, int n_wp, int n_c, int lanes, int batch_tiles)
             split_pays(c, n_wp, n_c, lanes, L.staged, tiles, alone))
             return kOccSplit;
     }
-    // the other compilations exist for 8 and 16 lanes per sample
-    if (lanes < 8) return kOccDefault;
-    return h->occ_req >= 0 ? h->occ_req : auto_occ(c, n_c);
+    return k_batch_occ(h, n_c, lanes);
+}
+
+// Whether the split kernel could run an instance of a batch at 16 lanes per
+// sample, where it exists for every configuration.
+static bool split_could(const mppi_t* h, int n_wp, int lanes)
+{
+    return lanes == 16 && !h->no_cull && h->occ_req < 0 &&
+           split_layout(h->cfg.T, n_wp, 16, h->cfg.per_step_weights).total <= kSplitLds;
 }
 
 // ---- profiling --------------------------------------------------------------------
@@ -829,12 +842,14 @@ void choose_eps_stage(InstDesc& d, bool alone, int allowed)
 }
 
 // Descriptor of one iteration of handle h from state x0 on the scene at
-// `scene` (device), staged relative to `origin`; batch_tiles as for occ_choice.
+// `scene` (device), staged relative to `origin`, launched alone (occ < 0) or in a
+// batch with iteration kernel occ.
 void fill_desc(InstDesc& d, const mppi_t* h, const double x0[4], const double origin[2],
                const unsigned char* scene, const SceneLayout& L, int n_wp, int n_c, int shift,
-               int batch_tiles)
+               int occ)
 {
     const mppi_config& c = h->cfg;
+    const bool alone = occ < 0;
     memset(&d, 0, sizeof d);
     d.K = c.K;
     d.T = c.T;
@@ -845,7 +860,7 @@ void fill_desc(InstDesc& d, const mppi_t* h, const double x0[4], const double or
     // two or more waves per SIMD (256 compute units x 4): the block-ordered
     // wave priority pays; with fewer it only costs its instructions
     d.wave_prio = (long)c.K * d.lanes >= 2L * 1024 * 64 ? 1 : 0;
-    d.occ = occ_choice(h, n_wp, n_c, d.lanes, batch_tiles);
+    d.occ = alone ? occ_choice(h, n_wp, n_c, d.lanes, 0) : occ;
     d.dt = (float)c.dt;
     d.inv_dt = (float)(1.0 / c.dt);
     d.inv_L = (float)(1.0 / c.wheelbase);
@@ -902,7 +917,7 @@ void fill_desc(InstDesc& d, const mppi_t* h, const double x0[4], const double or
     d.q = h->q;
     d.Stk = h->Stk;
     d.st = h->st;
-    choose_eps_stage(d, batch_tiles == 0, stage_allowed(h, n_c));
+    choose_eps_stage(d, alone, stage_allowed(h, n_c));
 }
 
 // ---- batched launches ---------------------------------------------------------------
@@ -1005,7 +1020,7 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
     unsigned char* host = ws->stage[b];
 
     // group by kernel variant, longest tiles first inside a group
-    std::vector<int> order(n), cls(n);
+    std::vector<int> order(n), cls(n), occ(n);
     std::vector<double> work(n);
     long total = 0;  // tiles of the batch
     for (int i = 0; i < n; ++i) {
@@ -1014,7 +1029,20 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
         total += ((long)hs[i]->cfg.K * cls[i] + kBlock - 1) / kBlock;
     }
     if (total > (1L << 30)) return fail(MPPI_E_INVALID, "batch too large");
+    // Instances at 16 lanes that either kernel can run all take the one that more
+    // of their tiles would, where the others are few: a launch of its own for a
+    // few tiles leaves most of the chip idle (8 instances, one of them of 4096 x
+    // 40: 151 us with it in k_batch and the others in the split kernel, 139 so).
+    constexpr long kFewTiles = 1024;
     const int batch_tiles = (int)total;
+    long in_split = 0, in_k_batch = 0;
+    for (int i = 0; i < n; ++i) {
+        const int nw = scenes ? scenes[i].n_waypoints : hs[i]->n_wp;
+        const int nc = scenes ? scenes[i].n_circles : hs[i]->n_c;
+        occ[i] = occ_choice(hs[i], nw, nc, cls[i], batch_tiles);
+        if (split_could(hs[i], nw, cls[i])) (occ[i] == kOccSplit ? in_split : in_k_batch) += (hs[i]->cfg.K + 15) / 16;
+    }
+    const bool together = in_split && in_k_batch && std::min(in_split, in_k_batch) < kFewTiles;
     for (int i = 0; i < n; ++i) {
         const mppi_config& c = hs[i]->cfg;
         const int nw = scenes ? scenes[i].n_waypoints : hs[i]->n_wp;
@@ -1022,9 +1050,10 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
         const int g = cls[i];
         const int gi = g == 1 ? 0 : g == 2 ? 1 : g == 4 ? 2 : g == 8 ? 3 : 4;
         order[i] = i;
-        const int occ = occ_choice(hs[i], nw, nc, g, batch_tiles);
-        cls[i] = 50 * occ + 25 * (c.model ? 1 : 0) +
-                 5 * (occ == kOccSplit && c.per_step_weights ? 0 : gi) + active_ego(c.n_ego, nc);
+        if (together && split_could(hs[i], nw, g))
+            occ[i] = in_split >= in_k_batch ? kOccSplit : k_batch_occ(hs[i], nc, g);
+        cls[i] = 50 * occ[i] + 25 * (c.model ? 1 : 0) +
+                 5 * (occ[i] == kOccSplit && c.per_step_weights ? 0 : gi) + active_ego(c.n_ego, nc);
         work[i] = (double)c.T * (73.0 + 6.0 * nw + 7.0 * c.n_ego * nc);
     }
     // The split kernel without the circles waves is launched for instances that
@@ -1062,10 +1091,10 @@ mppi_status batch_enqueue(BatchWs* ws, hipStream_t stream, mppi_t* const* hs, co
             const double origin[2] = {x0[0], x0[1]};
             write_scene(host + soff[i], lay[i], hi->cfg, origin, &scenes[i]);
             fill_desc(descs[j], hi, x0, origin, ws->arena + soff[i], lay[i], scenes[i].n_waypoints,
-                      scenes[i].n_circles, sh, batch_tiles);
+                      scenes[i].n_circles, sh, occ[i]);
         } else {
             fill_desc(descs[j], hi, x0, hi->origin, hi->scene, hi->lay, hi->n_wp, hi->n_c, sh,
-                      batch_tiles);
+                      occ[i]);
         }
         if (ex) {
             descs[j].S = ex->S;
@@ -1281,7 +1310,7 @@ mppi_status mppi_step_resident(mppi_t* h, const double x0[4])
         if (!isfinite(x0[i])) return fail(MPPI_E_INVALID, "x0[%d] is not finite", i);
     changes_results(h);
     InstDesc d;
-    fill_desc(d, h, x0, h->origin, h->scene, h->lay, h->n_wp, h->n_c, 0, 0);
+    fill_desc(d, h, x0, h->origin, h->scene, h->lay, h->n_wp, h->n_c, 0, -1);
     hipEvent_t a = nullptr;
     if ((s = record_launch(h, 0, &a)) != MPPI_OK) return s;
     hipEvent_t a2 = nullptr;

@@ -173,7 +173,7 @@ extern "C" mppi_status mppi_step_static(const mppi_config* cfg, const double x0[
     HIP_TRY(hipMemcpyAsync(inst.scene, g_stage, lay.bytes, hipMemcpyHostToDevice, stream));
 
     InstDesc d;
-    fill_desc(d, &inst, x0, origin, inst.scene, lay, n_wp, n_c, 0, 0);  // alone, as mppi_step_resident
+    fill_desc(d, &inst, x0, origin, inst.scene, lay, n_wp, n_c, 0, -1);  // alone, as mppi_step_resident
     hipLaunchKernelGGL(k_static_begin, dim3(1), dim3(64), 0, stream, inst.st, (unsigned long long)n_iter);
     HIP_TRY(hipGetLastError());
     HIP_TRY(launch_batch(d.lanes, active_ego(d.n_ego, d.n_c), d.model, d.occ, d.per_step, &d, nullptr, 0,

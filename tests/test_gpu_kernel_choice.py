@@ -125,3 +125,38 @@ def _check(lanes, n, K, T, n_c, ps, split, waypoints):
     finally:
         for pl in reversed(pls):
             pl.close()
+
+
+@pytest.mark.parametrize("shapes,asked,kernels", [
+    # few tiles for either kernel go with the many of the other
+    ([(4096, 40), (8192, 100), (8192, 100), (2048, 60)], {}, [SPLIT] * 4),
+    ([(8192, 20), (8192, 24), (1024, 100), (2048, 20)], {}, [0] * 4),
+    # each its own where both are many; a compilation asked for is kept
+    ([(16400, 20), (16400, 100)], {}, [0, SPLIT]),
+    ([(4096, 40), (8192, 100), (8192, 100)], {0: 0, 1: 1}, [0, 1, SPLIT]),
+])
+def test_few_tiles_of_a_batch_go_with_the_others(shapes, asked, kernels):
+    """Kernels of a batch of uneven instances at 16 lanes per sample; each has its
+    bits from alone."""
+    mppi = _mppi()
+    insts = [scenes.tiny(K=K, T=T, n_c=9, seed=i) for i, (K, T) in enumerate(shapes)]
+    lead = mppi.Planner(insts[0]["params"], lanes=16)
+    pls = [lead] + [mppi.Planner(s["params"], lanes=16, hip_stream=lead.stream()) for s in insts[1:]]
+    print("  case:", shapes, asked, flush=True)
+    try:
+        for i, occ in asked.items():
+            pls[i].set_occupancy(occ)
+        mppi.step_batch(pls, np.array([s["x0"] for s in insts]),
+                        [(s["waypoints"], s["circles"]) for s in insts])
+        got = [pl.kernel() for pl in pls]
+        # (k_batch's compilation is the tuning table's unless one is asked for)
+        assert [SPLIT if k == SPLIT else asked.get(i, 0) for i, k in enumerate(got)] == kernels
+        assert all(got[i] == occ for i, occ in asked.items())
+        for pl, s in zip(pls, insts):
+            with mppi.Planner(s["params"], lanes=16) as ref:
+                ref.step(s["x0"], s["waypoints"], s["circles"])
+                assert np.array_equal(pl.costs(), ref.costs())
+                assert np.array_equal(pl.controls(), ref.controls())
+    finally:
+        for pl in reversed(pls):
+            pl.close()
