@@ -189,8 +189,9 @@ mppi_status mppi_step_batch(mppi_t* const* hs, const double* x0s, const mppi_sce
  * mppi_sync, mppi_get_controls, mppi_get_state, mppi_get_iter_stats and
  * mppi_get_trajectory have the device write their results into a small
  * pinned host buffer of the handle, made by the first of them that reads
- * a result (mppi_sync reads one only once the handle has stepped);
- * MPPI_E_NOMEM if it cannot be made. */
+ * a result (mppi_sync reads one only once the handle has stepped) or by the
+ * first batch of 16 handles or more, which leaves its results there;
+ * MPPI_E_NOMEM if one that reads cannot make it. */
 mppi_status mppi_sync(mppi_t* h);
 
 /* Copy U (the nominal controls, [T][2] = (a, delta)) into out; n >= 2T.
@@ -247,18 +248,22 @@ mppi_status mppi_get_iter_stats(mppi_t* h, mppi_iter_stats* out);
  * let the library pick from its tuning table. */
 mppi_status mppi_set_lanes_per_sample(mppi_t* h, int32_t lanes);
 
-/* LDS copy of each tile's applied perturbations for its weighted sums:
+/* LDS copy of each tile's applied perturbations for its weighted sums, in
+ * steps whose kernel is 0 or 1 (mppi_get_kernel):
  * -1 (default) the tuning table's choice for the instance's shape, 0 never
  * (the sums read them back from L2), 1 whenever the copy fits the LDS.
  * Results are identical bit for bit. */
 mppi_status mppi_set_staging(mppi_t* h, int32_t mode);
 
-/* Compilation of the iteration kernel (the parallel rollout of Alg. 1,
- * Sec. III-A): -1 (default) the tuning table's choice for the instance's
- * shape, 0 the default register budget, 1 the variant compiled for five
- * waves per SIMD (instances with far more waves than the GPU holds at
- * once; at 8 and 16 lanes per sample, other shapes use 0).  Results are
- * identical bit for bit.  MPPI_E_INVALID for other values. */
+/* Iteration kernel (the parallel rollout of Alg. 1, Sec. III-A): -1 (default)
+ * the library's choice for the instance's shape and the size of the launch --
+ * the kernel that gives the parts of a rollout to different waves where it is
+ * the faster, else the tuning table's compilation of the one that gives a
+ * sample's rollout to one wave.  0 and 1 ask for that one, which is the slower
+ * for most shapes: 0 with the default register budget, 1 compiled for five
+ * waves per SIMD (instances with far more waves than the GPU holds at once; at
+ * 8 and 16 lanes per sample, other shapes use 0).  Results are identical bit
+ * for bit.  MPPI_E_INVALID for other values. */
 mppi_status mppi_set_occupancy(mppi_t* h, int32_t mode);
 
 /* The iteration kernel of the handle's last step: 0 or 1 as for
@@ -267,10 +272,11 @@ mppi_status mppi_set_occupancy(mppi_t* h, int32_t mode);
  * MPPI_E_NOT_READY before the first step. */
 mppi_status mppi_get_kernel(mppi_t* h, int32_t* kernel);
 
-/* Wave-level culling of the two scans of the stage cost (on by default):
- * waypoint chunks and obstacle circles that provably cannot change any
- * lane's tracking minimum or obstacle cost are skipped.  Results are
- * identical bit for bit; off (0) runs the full scans. */
+/* Culling of the two scans of the stage cost, by wave or by each sample's 16
+ * consecutive steps (on by default): waypoint chunks and obstacle circles that
+ * provably cannot change the tracking minimum or the obstacle cost of any of
+ * its states are skipped.  Results are identical bit for bit; off (0) runs the
+ * full scans (kernel 0 or 1). */
 mppi_status mppi_set_culling(mppi_t* h, int32_t on);
 
 /* The HIP stream the handle enqueues on (as void*). */

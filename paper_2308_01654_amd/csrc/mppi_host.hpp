@@ -75,7 +75,7 @@ struct mppi {
     bool own_stream = false;
     int lanes_req = 0;  // 0 = tuning table
     int stage_req = -1; // -1 = tuning table, 0 = no LDS copy of the perturbations, 1 = when it fits
-    int occ_req = -1;   // -1 = tuning table, else kOccDefault or kOccHigh
+    int occ_req = -1;   // -1 = the library's choice, else the compilation of k_batch asked for
     int no_cull = 0;    // 1: full waypoint and circle scans
     int last_lanes = 0;
     int last_occ = -1;  // iteration kernel of the last step (kOcc...), -1: none yet
@@ -172,13 +172,12 @@ void choose_eps_stage(InstDesc& d, bool alone, int allowed);
 // the tuning table's choice for its shape).
 int stage_allowed(const mppi_t* h, int n_c);
 int auto_stage(const mppi_config& c, int n_c);
-// The iteration kernel an instance is launched with, alone or in a batch: the
-// handle's request (a compilation of k_batch), else the split kernel where it
-// applies, else the tuning table's choice (kOccDefault when it has no such
-// column; kOccDefault below 8 lanes per sample).
 int auto_occ(const mppi_config& c, int n_c);
-// batch_tiles: the tiles of the batch it is launched in, 0 for an instance
-// launched alone.
+// The iteration kernel an instance is launched with: the handle's request (a
+// compilation of k_batch), else the split kernel where it pays, else the tuning
+// table's compilation of k_batch (kOccDefault when it has no such column, and
+// below 8 lanes per sample).  batch_tiles: the tiles of the batch it is launched
+// in, 0 for an instance launched alone.
 int occ_choice(const mppi_t* h, int n_wp, int n_c, int lanes, int batch_tiles);
 mppi_status ws_create(BatchWs** out);
 void ws_destroy(BatchWs* b);

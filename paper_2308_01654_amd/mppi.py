@@ -362,7 +362,9 @@ class Planner:
         check(load().mppi_set_staging(self.h, int(mode)))
 
     def set_occupancy(self, mode):
-        """-1: tuning table, 0: default kernel, 1: the five-waves-per-SIMD kernel."""
+        """-1: the library's choice (the split kernel where it is the faster); 0, 1: the
+        kernel that gives a sample's rollout to one wave, 1 compiled for five waves per
+        SIMD."""
         check(load().mppi_set_occupancy(self.h, int(mode)))
 
     def kernel(self):
