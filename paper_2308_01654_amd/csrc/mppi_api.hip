@@ -616,13 +616,13 @@ static volatile uint32_t* staged_word(mppi_t* h, int i)
     return reinterpret_cast<volatile uint32_t*>(h->staging[i] + align_up(h->scene_cap, 64));
 }
 
-// The capture that h's stream is in (its number), or 0.
+// The capture that h's stream is in (its number and one), or 0.
 static unsigned long long capture_of(mppi_t* h)
 {
     hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
     unsigned long long id = 0;
     if (hipStreamGetCaptureInfo(h->stream, &c, &id) != hipSuccess) (void)hipGetLastError();
-    return c == hipStreamCaptureStatusActive ? id : 0;
+    return c == hipStreamCaptureStatusActive ? id + 1 : 0;
 }
 
 // Waits until the device has read the last upload from staging buffer b.  Only
